@@ -30,6 +30,11 @@ CFLAGS = [
     "-Wno-unused-command-line-argument", "-Wno-unused-result",
     "-I" + os.path.join(HERE, "..", "include"),
 ]
+# kernels that keep tiles in MFMA accumulators between other uses: with the
+# accumulators in the common registers no copies to and from the separate
+# accumulation registers are made
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+FILE_FLAGS = {"inertia.hip": VGPR_FORM}
 LDFLAGS = ["-shared", f"--offload-arch={ARCH}"]
 # host-only sanitizers: each -fsanitize= applies to the host pass alone
 SAN_FLAGS = [
@@ -63,7 +68,7 @@ def _compile(src: str, force: bool = True, sanitize: bool = False) -> str:
         if os.path.getmtime(obj) > max(os.path.getmtime(d) for d in deps):
             return obj
     flags = [f for f in CFLAGS if f != "-O3"] + SAN_FLAGS if sanitize else CFLAGS
-    cmd = [HIPCC, *flags, "-c", src, "-o", obj]
+    cmd = [HIPCC, *flags, *FILE_FLAGS.get(os.path.basename(src), []), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr[-6000:]}")

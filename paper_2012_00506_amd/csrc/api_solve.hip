@@ -108,9 +108,10 @@ extern "C" int fb_device_info(int32_t* cus, char* name, int32_t cap) {
   return 0;
 }
 
-extern "C" int band_inertia(const fb_band* B, int32_t nshift, const double* shifts,
-                            int32_t* n_neg, int32_t* n_zero, int32_t* n_pos, void* work,
-                            size_t* lwork, void* stream) {
+namespace fb {
+int inertia_call(const fb_band* B, int32_t nshift, const double* shifts, int32_t* n_neg,
+                 int32_t* n_zero, int32_t* n_pos, void* work, size_t* lwork, bool split,
+                 void* stream) {
   if (check_band(B)) return -1;
   if (nshift < 0) return -2;
   if (nshift > 0 && !shifts) return -3;
@@ -124,7 +125,7 @@ extern "C" int band_inertia(const fb_band* B, int32_t nshift, const double* shif
   FB_TRY(ingest_band(B, bd, ar, st, false));
   double* sh = ar.take<double>(std::max(nshift, 1));
   int32_t* cnt = ar.take<int32_t>(3 * (size_t)std::max(nshift, 1));
-  size_t scb = inertia_scratch_bytes(bd, nshift);
+  size_t scb = split ? inertia_scratch_bytes(bd, nshift) : 0;
   void* scratch = scb ? (void*)ar.take<char>(scb) : nullptr;
   if (work == nullptr) {
     *lwork = ar.used;
@@ -145,6 +146,13 @@ extern "C" int band_inertia(const fb_band* B, int32_t nshift, const double* shif
     if (n_pos) n_pos[i] = h[3 * i + 2];
   }
   return 0;
+}
+}  // namespace fb
+
+extern "C" int band_inertia(const fb_band* B, int32_t nshift, const double* shifts,
+                            int32_t* n_neg, int32_t* n_zero, int32_t* n_pos, void* work,
+                            size_t* lwork, void* stream) {
+  return inertia_call(B, nshift, shifts, n_neg, n_zero, n_pos, work, lwork, true, stream);
 }
 
 namespace fb {

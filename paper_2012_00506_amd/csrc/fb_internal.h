@@ -166,10 +166,16 @@ int check_finite_blocks(int nblk, const void* const* P, const int64_t* ld, const
                         int64_t rows, bool cplx, double* part_dev, hipStream_t st);
 constexpr int kFiniteParts = 64;
 
-// inertia for nshift shifts (dev shifts array), counts dev int32 x3
+// inertia for nshift shifts (dev shifts array), counts dev int32 x3; scratch:
+// inertia_scratch_bytes(bd, at least nshift), or nullptr where there is none
 int launch_inertia(const Band& bd, int nshift, const double* shifts_dev,
                    int32_t* cnt_dev, void* scratch, hipStream_t st);
 size_t inertia_scratch_bytes(const Band& bd, int nshift);
+// band_inertia; split = false takes no scratch beyond the band copy, the
+// shifts and the counts
+int inertia_call(const fb_band* B, int32_t nshift, const double* shifts, int32_t* n_neg,
+                 int32_t* n_zero, int32_t* n_pos, void* work, size_t* lwork, bool split,
+                 void* stream);
 
 int device_cus();
 

@@ -63,8 +63,10 @@ __device__ __forceinline__ c128 sub_prod(c128 v, c128 a, c128 u) {
   return mk(fma(a.y, u.y, fma(-a.x, u.x, v.x)), fma(-a.y, u.x, fma(-a.x, u.y, v.y)));
 }
 // 1 / d: the hardware estimate, two Newton steps and a last one that rounds
-// (50 cycles where the general division takes 77)
+// (50 cycles where the general division takes 77), in the range in which they
+// hold
 __device__ __forceinline__ double recip(double d) {
+  if (__builtin_expect(!(fabs(d) > 1e-290 && fabs(d) < 1e290), 0)) return 1.0 / d;
   double r = __builtin_amdgcn_rcp(d);
 #pragma unroll
   for (int i = 0; i < 3; ++i) r = fma(fma(-d, r, 1.0), r, r);

@@ -2,15 +2,9 @@
 // (one factorisation per integration node, Section 2.2, eq:feast_L2),
 // producing the block form consumed by the block solves.
 //
-// One workgroup per system.  The active part of the elimination at step j is
-// rows j..j+b and columns j..j+2b (U widens to bandwidth 2b under row
-// interchanges); it lives in an MR x MC circular window (MR = b+2,
-// MC = 2b+2) indexed by (physical row, column mod MC).  A logical row i
-// maps to a physical row through phys[i mod MR] (held as the row's element
-// offset, physical row times MC), so a row interchange is an O(1) swap of
-// two table entries.  Row j+b+1 enters during step j into the
-// physical row freed by row j-1, and its columns j+1 .. j+2b+1 are exactly
-// the window's columns at step j+1.
+// One workgroup per system.  The active part of the elimination of columns
+// j .. j+7 is rows j .. j+b+7 and columns j .. j+2b+7 (U widens to bandwidth
+// 2b under row interchanges).
 //
 // Output per block k of b columns (the window rows kb .. kb+2b-1):
 //   perm  the net row permutation of the block's interchanges,
@@ -24,11 +18,9 @@
 // G2 = U(k,k)^{-1} U(k,k+2), so that each step of every solve sweep is one
 // set of independent dense b x b products (see solve.hip).
 //
-// Within a block the multipliers are written to a per-system scratch under a
-// storage row that follows each window row through the interchanges (an O(1)
-// swap of two table entries), and gathered into row order once at the end of
-// the block; the entering row of the next step is fetched from B while the
-// current step runs.
+// Within a block the multipliers are written to a per-system scratch under
+// their row's position at the block's start (or entry), and gathered into row
+// order once after the end of the block.
 #include "prof.h"
 #include "solve_job.h"
 #include "solve_kernel.h"
@@ -38,393 +30,755 @@ namespace fb {
 static const int kLuThreads = 512;
 static const size_t kLdsBudget = 160 * 1024;
 
-template <typename R>
-struct FactorOut {
-  cx<R>* mats;     // nsys * K * 5 * b * b
-  int16_t* perm;   // nsys * K * 2b
-  int32_t* info;   // nsys
-  cx<R>* lscr;     // nsys * 2 * 2b * b: multipliers of the current block by storage row
-};
-
-template <typename R, typename PB>
-__device__ __forceinline__ cx<R> shifted_entry(PB Bd, int64_t n, int b, int64_t i, int64_t c,
-                                               c128 z) {
-  // A(i, c) of zI - B, padded with the identity beyond n
-  if (i >= n || c >= n) return mk<R>(i == c ? (R)1 : (R)0, (R)0);
-  int64_t d = i - c;
-  c128 v;
-  if (d >= 0) {
-    if (d > b) return mk<R>(0, 0);
-    c128 e = gld(Bd + d * n + c);
-    v = mk(-e.x, -e.y);
-  } else {
-    if (-d > b) return mk<R>(0, 0);
-    c128 e = gld(Bd + (-d) * n + i);
-    v = mk(-e.x, e.y);  // -conj(B(c, i))
-  }
-  if (d == 0) {
-    v.x += z.x;
-    v.y = z.y;  // the diagonal of B is real
-  }
-  return mk<R>((R)v.x, (R)v.y);
-}
-
 // ---- wave-wide reductions of wave 0 for the pivot search, by DPP lane moves
 // within rows of 16 lanes (xor 1, xor 2, half mirror, mirror) and reads of
 // lanes 0, 16, 32 and 48; every lane of the wave must be active.
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
-  return ((uint64_t)dpp32<CTRL>((uint32_t)(v >> 32)) << 32) | dpp32<CTRL>((uint32_t)v);
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
 __device__ __forceinline__ uint64_t rdlane64(uint64_t v, int l) {
   return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
 }
-template <typename U, bool MAX>
-__device__ __forceinline__ U wave_reduce(U v) {
-  auto pick = [](U a, U b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
-  if constexpr (sizeof(U) == 8) {
-    v = pick(v, dpp64<0xB1>(v));   // quad_perm [1,0,3,2]
-    v = pick(v, dpp64<0x4E>(v));   // quad_perm [2,3,0,1]
-    v = pick(v, dpp64<0x141>(v));  // row_half_mirror
-    v = pick(v, dpp64<0x140>(v));  // row_mirror
-    return pick(pick(rdlane64(v, 0), rdlane64(v, 16)), pick(rdlane64(v, 32), rdlane64(v, 48)));
-  } else {
-    v = pick(v, dpp32<0xB1>(v));
-    v = pick(v, dpp32<0x4E>(v));
-    v = pick(v, dpp32<0x141>(v));
-    v = pick(v, dpp32<0x140>(v));
-    auto rd = [&](int l) { return (U)__builtin_amdgcn_readlane((int)v, l); };
-    return pick(pick(rd(0), rd(16)), pick(rd(32), rd(48)));
-  }
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v) {
+  auto pick = [](uint32_t a, uint32_t b) { return MAX ? max(a, b) : min(a, b); };
+  v = pick(v, dpp32<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = pick(v, dpp32<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = pick(v, dpp32<0x141>(v));  // row_half_mirror
+  v = pick(v, dpp32<0x140>(v));  // row_mirror
+  auto rd = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+  return pick(pick(rd(0), rd(16)), pick(rd(32), rd(48)));
 }
-// bit pattern of a non-negative float or double: ordered as the value
-__device__ __forceinline__ uint32_t ordered_bits(float v) { return __float_as_uint(v); }
-__device__ __forceinline__ uint64_t ordered_bits(double v) {
-  return (uint64_t)__double_as_longlong(v);
+// leading and remaining 32 bits of the bit pattern of a non-negative float or
+// double, whose order is the values'
+__device__ __forceinline__ uint32_t high_bits(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ uint32_t high_bits(double v) {
+  return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
+}
+__device__ __forceinline__ uint32_t low_bits(float) { return 0; }
+__device__ __forceinline__ uint32_t low_bits(double v) {
+  return (uint32_t)__double_as_longlong(v);
 }
 
-// The elimination window: wholly in LDS, or split at element offset `split`
-// (a whole number of physical rows) with the leading rows in LDS and the rest
-// in the system's global scratch, so that only rows past the split add to
-// the per-step global traffic and the cache footprint.  The split form's
-// accesses are flat ones.
-template <typename R, bool USE_LDS>
-struct LuWindow {
-  cx<R>* l;
-  cx<R>* g;
-  int split;
-  __device__ __forceinline__ cx<R>& operator[](int e) const {
-    if constexpr (USE_LDS)
-      return l[e];
-    else
-      return *(e < split ? l + e : g + e);
-  }
+// ---------------------------------------------------------------- elimination
+// Panels of kP columns of the band padded to bandwidth NB.  The window holds
+// MT x 16 physical rows (the NB + kP logical rows a panel can touch, in no
+// order) by NCB x 16 columns (block column c / 16 mod NCB).  A row stays in
+// its physical slot until it becomes a pivot row; the slot then takes an
+// entering row, so that interchanges move nothing and every update is a
+// product over all physical rows.
+//
+// Step s applies panel s to the right and factors panel s + 1:
+//   1. the block column that holds panel s + 1, a row tile per wave (its
+//      pivot rows solved with the panel's unit lower triangle, the rest
+//      updated on MFMA, the entering rows put into the freed slots),
+//   2. wave 0 factors panel s + 1 in registers (lane = row, up to NR rows
+//      per lane); the other waves take the remaining block columns one by
+//      one from a counter in LDS, with the panel's rows of U, its
+//      multipliers and the previous block's gather.
+// The row tiles that do not fit LDS live in the system's global scratch.
+//
+// What bounds it: up to b = 64 the panel chain of wave 0 (pivot search,
+// reciprocal, broadcast and update of one column after the other, about 1 000
+// cycles a column) and the block column that it waits for, above that the
+// updates of one CU and, in complex128, the row tiles in global memory.  Eight
+// columns per panel: the chain's own update work grows with the panel, the
+// window's traffic falls with it.  Before, one column and one rank-one update
+// per two barriers.  LU per column, before -> now: complex64 b = 64 3.3 -> 0.75
+// us, b = 128 10.7 -> 1.7 us; complex128 b = 30 2.8 -> 0.9 us, b = 64 3.9 ->
+// 1.1 us (one launch of 4 to 32 systems).
+constexpr int kP = 8;
+constexpr int kNoRow = 0x40000000;  // logical row of an empty slot
+
+template <typename R>
+struct LuArgs {
+  const c128* Bblk;
+  int64_t n;
+  int K;
+  const c128* zs;
+  cx<R>* mats;     // nsys * K * 5 * NB * NB
+  int16_t* perm;   // nsys * K * 2 NB
+  int32_t* info;   // nsys
+  cx<R>* lscr;     // nsys * 2 * 2 NB * NB: multipliers by window row, by block parity
+  cx<R>* gwin;     // nsys * (MT - LT) * 16 * LD
 };
 
-template <typename R, bool USE_LDS>
-__global__ void __launch_bounds__(kLuThreads)
-k_band_lu(const c128* __restrict__ Bd_, int64_t n, int b, int nb, int K,
-          const c128* __restrict__ zs, FactorOut<R> out, cx<R>* __restrict__ gwin, int wsplit) {
+// Geometry of the elimination window.  A 16 x 16 tile is stored in the
+// accumulator layout of the MFMA that updates it: the 64 lanes' four real
+// parts, then their four imaginary parts, in 16-byte pieces.
+template <typename R, int NB>
+struct LuShape {
+  static constexpr int MT = NB / 16 + 1;      // row tiles: NB + kP rows
+  static constexpr int NCB = NB / 8 + 1;      // block columns: 2 NB + 16
+  static constexpr int ROWS = 16 * MT;
+  static constexpr int NR = (NB + kP + 63) / 64;
+  static constexpr int UC = 16 * NCB + 2;     // row of the panel's rows of U
+  static constexpr int INTS = 4 + 2 * kP + 4 * NB + 2 * ROWS;
+  // counter, pivots, positions, rows; the panels (two), their pivot rows, U
+  static constexpr size_t HEAD =
+      ((INTS * sizeof(int) + 15) & ~(size_t)15) +
+      (2 * kP * ROWS + 2 * kP * kP + kP * UC) * sizeof(cx<R>);
+  static constexpr size_t TILE = 256 * sizeof(cx<R>) * (size_t)NCB;  // a row of tiles
+  static constexpr int FIT = (int)((kLdsBudget - HEAD) / TILE);
+  static constexpr int LT = FIT < MT ? FIT : MT;  // row tiles in LDS
+  static constexpr size_t LDS = HEAD + LT * TILE;
+  static constexpr size_t SCRATCH = (size_t)(MT - LT) * TILE;
+};
+// place of element (row, col) of a tile, in R; the imaginary part 256 further on
+template <typename R>
+__device__ __forceinline__ int tile_at(int row, int col) {
+  if constexpr (sizeof(R) == 4)
+    return (((row >> 2) & 3) * 16 + col) * 4 + (row & 3);
+  else
+    return ((row >> 3) & 1) * 128 + ((row & 3) * 16 + col) * 2 + ((row >> 2) & 1);
+}
+// a lane's part of a tile: real and imaginary accumulators
+template <typename R>
+struct LuTile {
+  typename MF<R>::V re, im;
+};
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+// 16 bytes per lane and access; GL: global memory
+template <bool GL>
+__device__ __forceinline__ void tile_load(LuTile<float>& c, const float* t, int lane) {
+  const f32x4* p = reinterpret_cast<const f32x4*>(t) + lane;
+  c.re = GL ? gld(p) : p[0];
+  c.im = GL ? gld(p + 64) : p[64];
+}
+template <bool GL>
+__device__ __forceinline__ void tile_store(float* t, const LuTile<float>& c, int lane) {
+  f32x4* p = reinterpret_cast<f32x4*>(t) + lane;
+  if (GL) {
+    gst(p, (f32x4)c.re);
+    gst(p + 64, (f32x4)c.im);
+  } else {
+    p[0] = c.re;
+    p[64] = c.im;
+  }
+}
+template <bool GL>
+__device__ __forceinline__ void tile_load(LuTile<double>& c, const double* t, int lane) {
+  const f64x2* p = reinterpret_cast<const f64x2*>(t) + lane;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const f64x2 x = GL ? gld(p + 64 * h) : p[64 * h];
+    const f64x2 y = GL ? gld(p + 128 + 64 * h) : p[128 + 64 * h];
+    c.re[2 * h] = x[0];
+    c.re[2 * h + 1] = x[1];
+    c.im[2 * h] = y[0];
+    c.im[2 * h + 1] = y[1];
+  }
+}
+template <bool GL>
+__device__ __forceinline__ void tile_store(double* t, const LuTile<double>& c, int lane) {
+  f64x2* p = reinterpret_cast<f64x2*>(t) + lane;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const f64x2 x = {c.re[2 * h], c.re[2 * h + 1]}, y = {c.im[2 * h], c.im[2 * h + 1]};
+    if (GL) {
+      gst(p + 64 * h, x);
+      gst(p + 128 + 64 * h, y);
+    } else {
+      p[64 * h] = x;
+      p[128 + 64 * h] = y;
+    }
+  }
+}
+// Barrier for what waves hand each other through LDS: outstanding global
+// stores are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <typename R>
+__device__ __forceinline__ R lane_value(R v, int l);
+template <>
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+}
+template <>
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __longlong_as_double((long long)rdlane64((uint64_t)__double_as_longlong(v), l));
+}
+
+// c ? a : b by parts (a choice between whole elements would go through memory)
+template <typename R>
+__device__ __forceinline__ cx<R> pick(bool c, cx<R> a, cx<R> b) {
+  return mk(c ? a.x : b.x, c ? a.y : b.y);
+}
+// x - l u: in fused multiply-adds, or (ORD) the product rounded before it is
+// subtracted
+template <bool ORD, typename R>
+__device__ __forceinline__ cx<R> csub(cx<R> x, cx<R> l, cx<R> u) {
+  if constexpr (ORD)
+    return mk(x.x - fma(l.x, u.x, -(l.y * u.y)), x.y - fma(l.y, u.x, l.x * u.y));
+  else
+    return mk(fma(l.y, u.y, fma(-l.x, u.x, x.x)), fma(-l.y, u.x, fma(-l.x, u.y, x.y)));
+}
+// 1 / u from |u|^2 = d: the hardware's estimate of 1 / d and Newton steps, the
+// last of which rounds; where d leaves the range in which they hold, the
+// general division
+__device__ __forceinline__ float recip_of(float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double recip_of(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) r = fma(fma(-d, r, 1.0), r, r);
+  return r;
+}
+template <typename R>
+__device__ __forceinline__ cx<R> inverse_of(cx<R> u, R d) {
+  constexpr R big = sizeof(R) == 4 ? (R)1e30f : (R)1e290;
+  if (__builtin_expect(d > 1 / big && d < big, 1)) {
+    // quotients with a last correction, which rounds them as a division does
+    const R r = recip_of(d), x = u.x * r, y = -u.y * r;
+    return mk<R>(fma(fma(-d, x, u.x), r, x), fma(fma(-d, y, -u.y), r, y));
+  }
+  return d > (R)0 ? cinv(u) : mk<R>(0, 0);
+}
+
+template <typename R, int NB>
+__global__ void __launch_bounds__(kLuThreads) k_band_lu(LuArgs<R> a) {
+  using C = cx<R>;
+  using G = LuShape<R, NB>;
+  constexpr int MT = G::MT, NCB = G::NCB, ROWS = G::ROWS, NR = G::NR, LT = G::LT, UC = G::UC;
+  constexpr int LROWS = 16 * LT, RPB = NB / 16, BB = NB * NB;
+  // Small blocks: every element takes its updates one after another in pivot
+  // order, each product rounded, as in an unblocked elimination.  The panels
+  // bound the kernel there, so that the matrix cores would gain nothing (and
+  // the FP64 matrix rate is that of the vector unit).
+  constexpr bool ORD = NB <= 48;
+  constexpr int NW = kLuThreads / 64;
   extern __shared__ __align__(16) char lds_raw[];
-  const int MR = b + 2, MC = 2 * b + 2;
-  const int s = blockIdx.x;
-  const int t = threadIdx.x;
-  const int64_t npad = (int64_t)K * nb;
-  const c128 z = zs[s];
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int sys = blockIdx.x;
+  const int n = (int)a.n, K = a.K;
+  const int npad = K * NB, steps = npad / kP;
+  const c128 z = a.zs[sys];
 
-  // LDS: phys[MR] int, idx[2][2nb] int, piv info[4], lrow[2][2nb] int,
-  // lvec[b+1] cx<R>, then the window
-  int* phys = reinterpret_cast<int*>(lds_raw);
-  int* idx = phys + MR;                   // two perm buffers (block parity)
-  int* pivp = idx + 4 * nb;               // [0] = pivot row of this step
-  int* lrow = pivp + 4;                   // two storage-row tables (block parity)
-  cx<R>* lvec = reinterpret_cast<cx<R>*>(lds_raw + ((sizeof(int) * (MR + 8 * nb + 4) + 15) & ~15));
-  // the window's memory is a compile-time choice, so that LDS accesses are
-  // LDS instructions rather than flat ones where the whole window fits
-  const LuWindow<R, USE_LDS> W{lvec + b + 1, USE_LDS ? nullptr : gwin + (size_t)s * MR * MC,
-                               wsplit};
-  const c128* Bd = Bd_;
+  int* cnt = reinterpret_cast<int*>(lds_raw);  // next unit of the step
+  int* ps = cnt + 4;                           // [2][kP] pivot slots of a panel
+  int* idx = ps + 2 * kP;                      // [2][2 NB] window row at each position of a block
+  int* meta = idx + 4 * NB;                    // [2][ROWS] window row | pivot step << 16, -1 empty
+  C* Lp = reinterpret_cast<C*>(lds_raw + ((G::INTS * sizeof(int) + 15) & ~(size_t)15));
+  C* Lt = Lp + 2 * kP * ROWS;                  // [2][kP][kP] the pivot rows of a panel
+  C* Ub = Lt + 2 * kP * kP;                    // [kP][UC] the panel's rows of U, from block column J
+  R* W = reinterpret_cast<R*>(Ub + kP * UC);   // [LT][NCB] tiles
+  R* gw = reinterpret_cast<R*>(a.gwin) + (size_t)sys * (MT - LT) * NCB * 512;
+  C* mats = a.mats + (size_t)sys * K * 5 * BB;
+  int16_t* permg = a.perm + (size_t)sys * K * 2 * NB;
+  C* lscr = a.lscr + (size_t)sys * 4 * BB;
 
-  cx<R>* mats = out.mats + (size_t)s * K * 5 * nb * nb;
-  int16_t* permg = out.perm + (size_t)s * K * 2 * nb;
-  const size_t bb = (size_t)nb * nb;
-  cx<R>* lscr = out.lscr + (size_t)s * 2 * 2 * bb;  // [parity][column][storage row]
-  int32_t* info = out.info;
+  const int c16 = lane & 15, g4 = lane >> 4;
 
-  // --- init: zero window, load rows 0..b, identity tables, zero block 0 scratch
-  for (int e = t; e < MR * MC; e += blockDim.x) W[e] = mk<R>(0, 0);
-  for (int e = t; e < MR; e += blockDim.x) phys[e] = e * MC;
-  for (int e = t; e < 2 * nb; e += blockDim.x) {
-    idx[e] = e;
-    lrow[e] = e;
-  }
-  for (size_t e = t; e < 2 * bb; e += blockDim.x) gst(lscr + e, mk<R>(0, 0));
-  if (t == 0) gst(info + s, 0);
-  __syncthreads();
-  {
-    int64_t top = (int64_t)b < npad - 1 ? b : npad - 1;
-    for (int e = t; e < (b + 1) * (2 * b + 1); e += blockDim.x) {
-      int64_t i = e / (2 * b + 1), c = e % (2 * b + 1);
-      if (i <= top && c < npad && c - i <= b && i - c <= b)
-        W[i * MC + c] = shifted_entry<R>(Bd, n, b, i, c, z);
-    }
-  }
-  __syncthreads();
-
-  // entering row of step j (row j+b+1, columns j+1 .. j+2b+1): entry
-  // e = t + q * kLuThreads of this thread, fetched one step ahead as the raw
-  // complex128 element of B it comes from (B(i, c) at d = i - c = b - e >= 0,
-  // B(c, i) above the diagonal), with a branch-free address, so that the
-  // loads stay in flight until the row is stored a step later
-  constexpr int ER = 2;  // 2b+1 <= 2 * kLuThreads for b <= 255
-  auto fetch_row = [&](c128* raw, int64_t jf) {
-    const int64_t inew = jf + b + 1;
-#pragma unroll
-    for (int q = 0; q < ER; ++q) {
-      const int e = t + q * kLuThreads;
-      const int64_t c = jf + 1 + e;
-      const int d = b - e;
-      const bool ok = e <= 2 * b && inew < n && c < n;
-      const int64_t off = d >= 0 ? (int64_t)d * n + c : (int64_t)(-d) * n + inew;
-      raw[q] = gld(Bd + (ok ? off : 0));
+  // element (row, col) of the tile in block column p of the window
+  auto wput = [&](int row, int p, int col, C v) {
+    if (LT == MT || row < LROWS) {
+      R* at = W + (((row >> 4) * NCB + p) * 512 + tile_at<R>(row, col));
+      at[0] = v.x;
+      at[256] = v.y;
+    } else {
+      R* at = gw + ((((row - LROWS) >> 4) * NCB + p) * 512 + tile_at<R>(row, col));
+      gst(at, v.x);
+      gst(at + 256, v.y);
     }
   };
-  // A(i, c) = z delta_ic - B(i, c) of the entering row from its raw element
-  // (identity beyond n, zero beyond the padded order)
-  auto row_entry = [&](c128 v, int64_t jf, int q) -> cx<R> {
-    const int64_t inew = jf + b + 1;
-    const int e = t + q * kLuThreads;
-    const int64_t c = jf + 1 + e;
-    const int d = b - e;
-    if (e > 2 * b || inew >= npad || c >= npad) return mk<R>(0, 0);
-    if (inew >= n || c >= n) return mk<R>(d == 0 ? (R)1 : (R)0, (R)0);
-    if (d == 0) return mk<R>((R)(z.x - v.x), (R)z.y);  // the diagonal of B is real
-    return d > 0 ? mk<R>((R)-v.x, (R)-v.y) : mk<R>((R)-v.x, (R)v.y);
+  // rows r .. of block row kb, block column cb (in units of NB): element
+  // (kb NB + r, cb NB + cc) of z I - B, identity beyond n, zero beyond K blocks
+  auto a_load = [&](int kb, int r, int cb, int cc) -> c128 {
+    const int s = cb - kb + 1;
+    const bool ok = kb < K && s >= 0 && s < 3;
+    return gld(a.Bblk + (size_t)(ok ? kb * 3 + s : 0) * BB + (cc * NB + r));
+  };
+  auto a_value = [&](c128 v, int kb, int r, int cb, int cc) -> C {
+    const int s = cb - kb + 1;
+    const bool ok = kb < K && s >= 0 && s < 3;
+    C x = pick(ok, mk<R>((R)-v.x, (R)-v.y), mk<R>(0, 0));
+    const bool in = kb * NB + r < n;
+    x = pick(ok && s == 1 && r == cc, mk<R>(in ? (R)(z.x - v.x) : (R)1, in ? (R)z.y : (R)0), x);
+    return x;
   };
 
-  // this thread's U-row entries e = t + q kLuThreads (e < 3 nb): block
-  // 2 + e / nb, column e % nb, as an element offset within block row k
-  constexpr int UR = 2;  // 3 nb <= 2 kLuThreads for nb <= 128
-  size_t uoff[UR];
+  // ---- the first window: rows 0 .. NB + kP - 1 in their own slots
+  for (int e = t; e < ROWS * 16 * NCB; e += kLuThreads) {
+    const int row = e / (16 * NCB), c = e % (16 * NCB);
+    C v = mk<R>(0, 0);
+    if (row < NB + kP)
+      v = a_value(a_load(row / NB, row % NB, c / NB, c % NB), row / NB, row % NB, c / NB, c % NB);
+    wput(row, c >> 4, c & 15, v);
+    if (c < kP) Lp[c * ROWS + row] = v;
+  }
+  for (int e = t; e < 2 * BB; e += kLuThreads) gst(lscr + e, mk<R>(0, 0));
+  __syncthreads();
+  if (w == 0) {
+    // ---- wave 0: the panels.  Panel s1 = s + 1 is factored while the other
+    // waves apply panel s; its columns were put into its place in Lp.
+    __builtin_amdgcn_s_setprio(3);
+    int lp[NR], wr[NR], first_zero = 0;  // logical and window row of the lane's slots
 #pragma unroll
-  for (int q = 0; q < UR; ++q) {
-    const int e = t + q * kLuThreads;
-    uoff[q] = (size_t)(2 + e / nb) * bb + (size_t)(e % nb) * nb;
+    for (int r = 0; r < NR; ++r) {
+      const int row = lane + 64 * r;
+      lp[r] = row < NB + kP && row < npad ? row : kNoRow;
+      wr[r] = lp[r];
+    }
+    int kb1 = 0, jj1 = 0;
+    for (int s1 = 0; s1 < steps; ++s1) {
+      const int j1 = kP * s1, kb0 = NB * kb1, parn = s1 & 1;
+      int* idxk = idx + (kb1 & 1) * 2 * NB;
+      C* Ln = Lp + parn * kP * ROWS;
+      C x[NR][kP];
+      int step[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int row = lane + 64 * r;
+        step[r] = lp[r] == kNoRow ? -1 : kP;
+        const int rr = row < ROWS ? row : 0;
+#pragma unroll
+        for (int c = 0; c < kP; ++c) x[r][c] = Ln[c * ROWS + rr];
+      }
+      if (jj1 == 0) {
+        for (int e = lane; e < 2 * NB; e += 64) idxk[e] = e;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) wr[r] = lp[r] - kb0;
+      }
+#pragma unroll
+      for (int k = 0; k < kP; ++k) {
+        // largest |x|^2 of the rows not yet pivots (a NaN counts as 0), ties
+        // to the lowest logical row: by the leading 32 bits, which nearly
+        // always decide
+        R v[NR];
+        uint32_t key[NR], best = 0;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          v[r] = fmax(fma(x[r][k].x, x[r][k].x, x[r][k].y * x[r][k].y), (R)0);
+          key[r] = step[r] == kP ? high_bits(v[r]) : 0;
+          best = max(best, key[r]);
+        }
+        best = wave_reduce<true>(best);
+        uint64_t m[NR];
+        int total = 0;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          m[r] = __builtin_amdgcn_ballot_w64(key[r] == best);
+          total += __builtin_popcountll(m[r]);
+        }
+        if (__builtin_expect(total > 1 || best == 0, 0)) {
+          uint32_t lo = 0, low = kNoRow;
+          bool top[NR];
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            top[r] = step[r] == kP && key[r] == best;
+            lo = max(lo, top[r] ? low_bits(v[r]) : 0u);
+          }
+          lo = wave_reduce<true>(lo);
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            top[r] = top[r] && low_bits(v[r]) == lo;
+            low = min(low, top[r] ? (uint32_t)lp[r] : (uint32_t)kNoRow);
+          }
+          low = wave_reduce<false>(low);
+#pragma unroll
+          for (int r = 0; r < NR; ++r)
+            m[r] = __builtin_amdgcn_ballot_w64(top[r] && (uint32_t)lp[r] == low);
+        }
+        // the pivot row's slot (wave-uniform) and its entries from column k on
+        int pr = 0, plp = 0;
+        R d = 0;
+        C u[kP];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          if (NR > 1 && m[r] == 0) continue;
+          const int pl = __builtin_ctzll(m[r]);
+          pr = pl + 64 * r;
+          d = lane_value(v[r], pl);
+          plp = __builtin_amdgcn_readlane(lp[r], pl);
+#pragma unroll
+          for (int c = k; c < kP; ++c)
+            u[c] = mk<R>(lane_value(x[r][c].x, pl), lane_value(x[r][c].y, pl));
+        }
+        if (!(d > (R)0) && first_zero == 0) first_zero = j1 + k + 1;
+        const C rp = inverse_of(u[k], d);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          // the interchange: the row at position j1 + k takes the pivot's place
+          const bool piv = pr == lane + 64 * r;
+          lp[r] = piv ? j1 + k : lp[r] == j1 + k ? plp : lp[r];
+          step[r] = piv ? k : step[r];
+          const bool live = step[r] == kP;
+          const C xk = x[r][k];
+          C l = mk(fma(xk.x, rp.x, -(xk.y * rp.y)), fma(xk.x, rp.y, xk.y * rp.x));
+          x[r][k] = pick(live, l, x[r][k]);
+          l = pick(live, l, mk<R>(0, 0));
+#pragma unroll
+          for (int c = k + 1; c < kP; ++c) x[r][c] = csub<ORD>(x[r][c], l, u[c]);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int row = lane + 64 * r;
+        if (row < ROWS) {
+#pragma unroll
+          for (int c = 0; c < kP; ++c) Ln[c * ROWS + row] = x[r][c];
+          meta[parn * ROWS + row] = step[r] < 0 ? -1 : wr[r] | (step[r] << 16);
+        }
+        if (step[r] == kP && jj1 + kP == NB) idxk[lp[r] - kb0] = wr[r];
+        if (step[r] >= 0 && step[r] < kP) {
+          ps[parn * kP + step[r]] = row;
+          idxk[jj1 + step[r]] = wr[r];
+#pragma unroll
+          for (int c = 0; c < kP; ++c) Lt[(parn * kP + step[r]) * kP + c] = x[r][c];
+          // the freed slot's entering row
+          const int in = j1 + kP + NB + step[r];
+          lp[r] = in < npad ? in : kNoRow;
+          wr[r] = lp[r] - kb0;
+        }
+      }
+      jj1 += kP;
+      if (jj1 == NB) {
+        jj1 = 0;
+        ++kb1;
+      }
+      lds_barrier();    // panel s1 is factored and panel s1 - 1 applied
+      lds_barrier();    // the panel's rows of U are formed
+      lds_barrier();    // the columns of panel s1 + 1 are updated
+    }
+    if (lane == 0) gst(a.info + sys, first_zero);
+    __syncthreads();
+    return;
   }
 
-  // update mapping: 2b columns in flight, kLuThreads / 2b row groups
-  const int ucols = 2 * b, ugrps = kLuThreads / ucols;
-  const int ucol = t % ucols, ugrp = t / ucols;
+  // ---- the other waves
+  __syncthreads();  // panel 0
+  // wave-uniform state of a step: column j0 = NB kblk + jj; block column J =
+  // j0 / 16, its place jp = J mod NCB in the window and tj = J mod RPB
+  int kblk = 0, jj = 0, jp = 0, tj = 0;
+  for (int s = 0; s < steps; ++s) {
+    const int par = s & 1, o = jj & 15;
+    const C* Lk = Lp + par * kP * ROWS;
+    const int* psk = ps + par * kP;
+    // entering rows j0 + kP + NB + k, k = 0 .. 7: block row kbe, rows re + k
+    const bool up = jj + kP == NB;
+    const int kbe = kblk + (up ? 2 : 1), re = up ? 0 : jj + kP;
+    // block column J + d: its place in the window; block and column in it
+    auto place = [&](int d) {
+      const int p = jp + d;
+      return p >= NCB ? p - NCB : p;
+    };
+    auto ent_load = [&](c128* e, int d) {
+      const int cb = kblk + (tj + d) / RPB, cc = ((tj + d) % RPB) * 16 + c16;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) e[q] = a_load(kbe, re + g4 + 4 * q, cb, cc);
+    };
+    auto ent_value = [&](const c128* e, int q, int d) {
+      const int cb = kblk + (tj + d) / RPB, cc = ((tj + d) % RPB) * 16 + c16;
+      return a_value(e[q], kbe, re + g4 + 4 * q, cb, cc);
+    };
+    auto ent_store = [&](const c128* e, int d) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) wput(psk[g4 + 4 * q], place(d), c16, ent_value(e, q, d));
+    };
+    // this lane's entries of the panel's rows of U in block column J + d as
+    // MFMA operands: rows g4 and g4 + 4
+    struct Bop {
+      R x[2], y[2], nx[2], ny[2];
+    };
+    auto b_load = [&](Bop& o2, int d) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const C u = Ub[(g4 + 4 * q) * UC + 16 * d + c16];
+        o2.x[q] = u.x;
+        o2.y[q] = u.y;
+        o2.nx[q] = -u.x;
+        o2.ny[q] = -u.y;
+      }
+    };
+    // the panel's rows of U in block column J + d to the factors
+    auto u_out = [&](int d) {
+      const int te = tj + d, k = lane & 7;  // te: within the three blocks of this row block
+      if (te >= 3 * RPB) return;
+      C* at = mats + (size_t)(kblk * 5 + 2 + te / RPB) * BB + ((te % RPB) * 16 * NB + jj + k);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int c = (lane >> 3) + 8 * q;
+        if (d == 0 && c < kP) continue;  // the panel's own columns
+        gst(at + c * NB, Ub[k * UC + 16 * d + c]);
+      }
+    };
+    // c -= L U for row tile rt
+    auto update = [&](LuTile<R>& c, int rt, const Bop& o2, int d) {
+      if constexpr (ORD) {
+#pragma unroll
+        for (int k = 0; k < kP; ++k) {
+          const C u = Ub[k * UC + 16 * d + c16];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const C f = Lk[k * ROWS + 16 * rt + MF<R>::row(lane, r)];
+            const C x = csub<true>(mk<R>(c.re[r], c.im[r]), f, u);
+            c.re[r] = x.x;
+            c.im[r] = x.y;
+          }
+        }
+        return;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const C f = Lk[(g4 + 4 * q) * ROWS + 16 * rt + c16];
+        c.re = MF<R>::mma(f.x, o2.nx[q], c.re);
+        c.im = MF<R>::mma(f.x, o2.ny[q], c.im);
+        c.re = MF<R>::mma(f.y, o2.y[q], c.re);
+        c.im = MF<R>::mma(f.y, o2.nx[q], c.im);
+      }
+    };
+    auto w_tile = [&](int rt, int p) { return W + (rt * NCB + p) * 512; };
+    auto g_tile = [&](int rt, int p) { return gw + ((rt - LT) * NCB + p) * 512; };
 
-  int first_zero = 0;
-  // running slots: row j sits in slot jr = j mod MR, column j in jcs = j mod MC;
-  // an offset below MR (MC) needs at most one wrap
-  int jr = 0, jcs = 0, k = 0, jj = 0;
-  auto rslot = [&](int off) { int v = jr + off; return v >= MR ? v - MR : v; };
-  auto cslot = [&](int off) { int v = jcs + off; return v >= MC ? v - MC : v; };
-  auto step = [&](int64_t j, const c128* cur, c128* nxt) {
-    // Row j+b+1 enters (columns j+1 .. j+2b+1, fetched during the last step)
-    // into the physical row that row j-1 left, and column j+2b+1 (the slot
-    // column j-1 left) is zeroed in rows j .. j+b: after this step's
-    // interchange rows j+1 .. j+b are among them, and the column is out of
-    // their band.  Both slots are free since the end of the last step and
-    // neither is read before the next barrier.  Storing them first, before
-    // this step issues its own global loads and stores, means the wait for
-    // the fetched row covers only memory operations a whole step old.
-    if (j + b + 1 < npad) {
-      const int pr = phys[rslot(b + 1)];
+    const int d1 = o == 0 ? 0 : 1;  // block column of panel s + 1
+    constexpr int NO = NW - 1, Q1 = (MT + NO - 1) / NO;
+    // unit u of the step: block column J + unit_col(u), the last of the steps
+    // that finish block column J its successor in that place
+    const int ntile = NCB - 1;
+    auto unit_col = [&](int u) { return o != 0 && u == ntile - 1 ? NCB : d1 + 1 + u; };
+    // ---- 1. the panel's rows of U, 64 columns per wave: the pivot rows
+    // solved with the panel's unit lower triangle
+    for (int ch = NW - 1 - w; 4 * ch + d1 < NCB; ch += NO) {
+      const int d = d1 + 4 * ch + g4;
+      const bool in = d < NCB;
+      const int p = in ? place(d) : 0;
+      const C* L = Lt + par * kP * kP;
+      C x[kP];
 #pragma unroll
-      for (int q = 0; q < ER; ++q) {
-        const int e = t + q * kLuThreads;
-        if (e <= 2 * b) W[pr + cslot(1 + e)] = row_entry(cur[q], j, q);
+      for (int k = 0; k < kP; ++k) {
+        // without branches, so that the rows in global memory are read together
+        const int row = __builtin_amdgcn_readfirstlane(psk[k]);
+        const int at = ((row >> 4) * NCB + p) * 512 + tile_at<R>(row, c16);
+        if constexpr (LT == MT) {
+          x[k] = mk(W[at], W[at + 256]);
+        } else {
+          const bool l = row < LROWS;
+          const int al = l ? at : 0, ag = l ? 0 : at - LT * NCB * 512;
+          x[k] = pick(l, mk(W[al], W[al + 256]), mk(gld(gw + ag), gld(gw + (ag + 256))));
+        }
+      }
+#pragma unroll
+      for (int k = 1; k < kP; ++k)
+#pragma unroll
+        for (int i = 0; i < k; ++i) x[k] = csub<ORD>(x[k], L[k * kP + i], x[i]);
+      if (in) {
+#pragma unroll
+        for (int k = 0; k < kP; ++k) Ub[k * UC + 16 * d + c16] = x[k];
       }
     }
-    {
-      const int cs = cslot(2 * b + 1);
-      for (int r = t; r <= b; r += blockDim.x) W[phys[rslot(r)] + cs] = mk<R>(0, 0);
+    // what the next parts need from memory
+    c128 e1[2], e0[2];
+    LuTile<R> v1[Q1];
+    ent_load(e1, d1);
+    ent_load(e0, unit_col(w - 1));
+    if (w - 1 < MT) {
+#pragma unroll
+      for (int q = 0; q < Q1; ++q) {
+        const int rt = w - 1 + NO * q;
+        if (rt < LT)
+          tile_load<false>(v1[q], w_tile(rt, place(d1)), lane);
+        else if (rt < MT)
+          tile_load<true>(v1[q], g_tile(rt, place(d1)), lane);
+      }
     }
-    if (j + 1 < npad) fetch_row(nxt, j + 1);
-    const int par = k & 1;
-    int* idxk = idx + par * 2 * nb;
-    int* lrk = lrow + par * 2 * nb;
-    cx<R>* scr = lscr + (size_t)par * 2 * bb;
-    const int64_t last = (j + b < npad - 1) ? j + b : npad - 1;
-    const int nr = (int)(last - j);               // rows below the pivot
-    const int64_t cend = (j + 2 * b < npad - 1) ? j + 2 * b : npad - 1;
-    const int nc = (int)(cend - j);               // columns right of the pivot
-    const int jc = jcs;
+    lds_barrier();
 
-    // ---- phase A (wave 0): pivot search, interchange, multipliers
-    if (t < 64) {
-      // largest |a|^2 of the column, ties to the lowest row: per lane over its
-      // rows in increasing order, then the largest value over the wave and
-      // the lowest row holding it
-      R best = (R)0;
-      int bi = 0x7fffffff;
-      for (int r = t; r <= nr; r += 64) {
-        cx<R> a = W[phys[rslot(r)] + jc];
-        R v = cabs2(a);
-        if (!(v >= (R)0)) v = (R)0;  // a NaN entry is never preferred
-        if (bi == 0x7fffffff || v > best) {
-          best = v;
-          bi = r;
+    // ---- 2. the block column of panel s + 1, a row tile per wave: that
+    // panel's columns go to its place in Lp
+    if (w - 1 < MT) {
+      const int po = o ^ kP;  // the panel's columns: po .. po + 7
+      C* Ln = Lp + (par ^ 1) * kP * ROWS + (c16 & 7) * ROWS;
+      const bool isp = (c16 & kP) == po;
+      Bop o2;
+      b_load(o2, d1);
+#pragma unroll
+      for (int q = 0; q < Q1; ++q) {
+        const int rt = w - 1 + NO * q;
+        if (rt >= MT) break;
+        update(v1[q], rt, o2, d1);
+        if (isp) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            Ln[16 * rt + MF<R>::row(lane, r)] = mk<R>(v1[q].re[r], v1[q].im[r]);
+        }
+        // the other half of a finished block column is not read again
+        if (o != 0) {
+          if (rt < LT)
+            tile_store<false>(w_tile(rt, place(d1)), v1[q], lane);
+          else
+            tile_store<true>(g_tile(rt, place(d1)), v1[q], lane);
         }
       }
-      {
-        const auto mb = wave_reduce<decltype(ordered_bits(best)), true>(ordered_bits(best));
-        const uint32_t cand =
-            (bi != 0x7fffffff && ordered_bits(best) == mb) ? (uint32_t)bi : 0x7fffffffu;
-        bi = (int)wave_reduce<uint32_t, false>(cand);
-      }
-      const int sj = jr, sp = rslot(bi);
-      const int physj_old = phys[sj], physp_old = phys[sp];
-      const int pw0 = jj + bi;
-      cx<R> piv = W[physp_old + jc];
-      cx<R> rp = cabs2(piv) > (R)0 ? cinv(piv) : mk<R>(0, 0);
-      for (int r = t + 1; r <= nr; r += 64) {
-        // after the interchange, window row jj + r holds the old row j when
-        // r == bi; its storage row moves with it
-        int pr = (r == bi) ? physj_old : phys[rslot(r)];
-        int srow = (r == bi) ? lrk[jj] : lrk[jj + r];
-        cx<R> l = W[pr + jc] * rp;
-        lvec[r - 1] = l;
-        gst(scr + (size_t)jj * 2 * nb + srow, l);
-      }
-      if (t == 0) {
-        phys[sj] = physp_old;
-        phys[sp] = physj_old;
-        int a = idxk[jj];
-        idxk[jj] = idxk[pw0];
-        idxk[pw0] = a;
-        a = lrk[jj];
-        lrk[jj] = lrk[pw0];
-        lrk[pw0] = a;
-        pivp[0] = pw0;
-        if (!(cabs2(piv) > (R)0) && first_zero == 0) first_zero = (int)(j + 1);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int row = psk[g4 + 4 * q];
+        const C x1 = ent_value(e1, q, d1);
+        if ((row >> 4) % NO != w - 1) continue;
+        if (isp) Ln[row] = x1;
+        if (o != 0) wput(row, place(d1), c16, x1);
       }
     }
-    __syncthreads();
+    if (t == 64) cnt[0] = NO;  // the first units are dealt out
+    lds_barrier();
 
-    // ---- phase B (all): U row, update, entering row, block end
-    const int prj = phys[jr];
-    {
-      // U row j: columns k nb .. k nb+3nb-1 of blocks U(k,k), U(k,k+1), U(k,k+2)
+    // ---- 3. the rest of the panel, while wave 0 factors the next one
+    const int ngather = jj == 0 && kblk > 0 ? NB / 4 : 0;
+    const int nzero = jj == kP ? NB / 8 : 0;
+    const int nunit = ntile + 2 + ngather + nzero;
+    auto grab = [&]() {
+      int u = 0;
+      if (lane == 0) u = atomicAdd(cnt, 1);
+      return __builtin_amdgcn_readfirstlane(u);
+    };
+    int unext = w - 1;
+    for (;;) {
+      int u = unext;
+      if (u >= nunit) break;
+      // the entering elements of this unit are on their way; the next unit's
+      // are asked for before this one's work
+      const c128 e[2] = {e0[0], e0[1]};
+      unext = grab();
+      if (unext < ntile) ent_load(e0, unit_col(unext));
+      if (u < ntile) {
+        if (o != 0 && u == ntile - 1) {
+          // block column J is finished: it becomes block column J + NCB
+          LuTile<R> c;
+          c.re = c.im = typename MF<R>::V{0, 0, 0, 0};
+          for (int rt = 0; rt < LT; ++rt) tile_store<false>(w_tile(rt, jp), c, lane);
+          for (int rt = LT; rt < MT; ++rt) tile_store<true>(g_tile(rt, jp), c, lane);
 #pragma unroll
-      for (int q = 0; q < UR; ++q) {
-        const int e = t + q * kLuThreads;
-        if (e >= 3 * nb) break;
-        const int co = e - jj;  // column offset from j
-        cx<R> v = mk<R>(0, 0);
-        if (co >= 0 && co <= nc) v = W[prj + cslot(co)];
-        gst(mats + (size_t)k * 5 * bb + uoff[q] + jj, v);
-      }
-      // rank-one update of rows j+1..last, columns j+1..cend: thread
-      // (ucol, ugrp) keeps one column and walks every ugrps-th row
-      if (ugrp < ugrps && ucol < nc) {
-        const int cs = cslot(ucol + 1);
-        const cx<R> u = W[prj + cs];
-        // rows in batches of UB: all loads of a batch before its stores (the
-        // rows are distinct physical rows, so nothing aliases)
-        constexpr int UB = 8;
-        for (int r0 = ugrp; r0 < nr; r0 += UB * ugrps) {
-          int a[UB];
-          cx<R> v[UB], l[UB];
-          if (r0 + (UB - 1) * ugrps < nr) {
-            // a whole batch in range (every batch but the last few steps'):
-            // no per-row tests
+          for (int q = 0; q < 2; ++q) wput(psk[g4 + 4 * q], jp, c16, ent_value(e, q, NCB));
+          continue;
+        }
+        const int d = d1 + 1 + u, p = place(d);
+        // row tiles in global memory, four at a time, their loads in flight
+        // over the tiles in LDS
+        constexpr int GT = MT - LT < 4 ? (MT - LT > 0 ? MT - LT : 1) : 4;
+        LuTile<R> v[GT];
+        if constexpr (LT < MT) {
 #pragma unroll
-            for (int q = 0; q < UB; ++q) a[q] = phys[rslot(r0 + q * ugrps + 1)] + cs;
+          for (int q = 0; q < GT; ++q) tile_load<true>(v[q], g_tile(LT + q, p), lane);
+        }
+        Bop o2;
+        b_load(o2, d);
 #pragma unroll
-            for (int q = 0; q < UB; ++q) {
-              v[q] = W[a[q]];
-              l[q] = lvec[r0 + q * ugrps];
-            }
+        for (int rt = 0; rt < LT; ++rt) {
+          LuTile<R> c;
+          tile_load<false>(c, w_tile(rt, p), lane);
+          update(c, rt, o2, d);
+          tile_store<false>(w_tile(rt, p), c, lane);
+        }
+        if constexpr (LT < MT) {
 #pragma unroll
-            for (int q = 0; q < UB; ++q) {
-              v[q].x -= l[q].x * u.x - l[q].y * u.y;
-              v[q].y -= l[q].x * u.y + l[q].y * u.x;
-              W[a[q]] = v[q];
-            }
-            continue;
-          }
+          for (int rt = LT; rt < MT; rt += GT) {
 #pragma unroll
-          for (int q = 0; q < UB; ++q) {
-            const int ro = r0 + q * ugrps;
-            a[q] = ro < nr ? phys[rslot(ro + 1)] + cs : 0;
-          }
-#pragma unroll
-          for (int q = 0; q < UB; ++q) {
-            const int ro = r0 + q * ugrps;
-            if (ro < nr) {
-              v[q] = W[a[q]];
-              l[q] = lvec[ro];
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < UB; ++q) {
-            const int ro = r0 + q * ugrps;
-            if (ro < nr) {
-              v[q].x -= l[q].x * u.x - l[q].y * u.y;
-              v[q].y -= l[q].x * u.y + l[q].y * u.x;
-              W[a[q]] = v[q];
-            }
+            for (int q = 0; q < GT; ++q)
+              if (rt + q < MT) {
+                update(v[q], rt + q, o2, d);
+                tile_store<true>(g_tile(rt + q, p), v[q], lane);
+                if (rt + GT + q < MT) tile_load<true>(v[q], g_tile(rt + GT + q, p), lane);
+              }
           }
         }
+        ent_store(e, d);
+        u_out(d);
+        continue;
       }
-      if (jj == nb - 1) {
-        // block k complete: multipliers into row order (P A_panel = Lh U),
-        // its permutation; fresh tables and scratch for block k+1
-        // (batches of GB elements per thread: all loads of a batch, then
-        // its stores)
-        constexpr int GB = 8;
-        const int nbb = 2 * (int)bb;  // 2 nb^2 <= 32768
-        for (int e0 = t; e0 < nbb; e0 += GB * kLuThreads) {
-          cx<R> v[GB];
+      u -= ntile;
+      if (u == 0) {
+        // multipliers by window row
+        C* scr = lscr + ((kblk & 1) * 2 * BB + jj * 2 * NB);
+        for (int row = lane; row < ROWS; row += 64) {
+          const int md = meta[par * ROWS + row];
+          if (md < 0) continue;
+          const int st = md >> 16, wrow = md & 0xffff;
 #pragma unroll
-          for (int q = 0; q < GB; ++q) {
-            const int e = e0 + q * kLuThreads;
-            const int ec = e < nbb ? e : 0;
-            const int c = ec / (2 * nb), wr = ec - c * 2 * nb;
-            v[q] = gld(scr + c * 2 * nb + lrk[wr]);
-          }
+          for (int i = 0; i < kP; ++i)
+            if (i < st) gst(scr + (i * 2 * NB + wrow), Lk[i * ROWS + row]);
+        }
+        continue;
+      }
+      if (u == 1) {
+        // the panel's rows of U outside the window's block columns: zeros,
+        // and the panel's own upper triangle
+        const int k = lane & 7;
+        u_out(d1);
+        for (int te = 0; te < 3 * RPB; ++te) {
+          if (te > tj && te < tj + NCB) continue;
+          C* at = mats + (size_t)(kblk * 5 + 2 + te / RPB) * BB + (te % RPB) * 16 * NB + jj + k;
 #pragma unroll
-          for (int q = 0; q < GB; ++q) {
-            const int e = e0 + q * kLuThreads;
-            if (e >= nbb) continue;
-            const int c = e / (2 * nb), wr = e - c * 2 * nb;
-            gst(mats + ((size_t)k * 5 + (wr < nb ? 0 : 1)) * bb + c * nb + (wr < nb ? wr : wr - nb),
-                v[q]);
+          for (int q = 0; q < 2; ++q) {
+            const int c = (lane >> 3) + 8 * q, cp = c - o;
+            if (te == tj && cp >= kP) continue;
+            C v = mk<R>(0, 0);
+            if (te == tj && cp >= k) v = Lt[(par * kP + k) * kP + cp];
+            gst(at + c * NB, v);
           }
         }
-        cx<R>* scr1 = lscr + (size_t)(par ^ 1) * 2 * bb;
-        for (size_t e = t; e < 2 * bb; e += blockDim.x) gst(scr1 + e, mk<R>(0, 0));
-        for (int e = t; e < 2 * nb; e += blockDim.x) {
-          gst(permg + (size_t)k * 2 * nb + e, (int16_t)idxk[e]);
-          idx[(par ^ 1) * 2 * nb + e] = e;
-          lrow[(par ^ 1) * 2 * nb + e] = e;
-        }
+        continue;
       }
+      u -= 2;
+      if (u < ngather) {
+        // the previous block's multipliers into row order (P A_panel = Lh U)
+        // and its permutation
+        const int kp = kblk - 1, pp = kp & 1;
+        const C* scr = lscr + pp * 2 * BB;
+        for (int e = lane; e < 2 * NB; e += 64) {
+          const int src = idx[pp * 2 * NB + e];
+          if (u == 0) gst(permg + (size_t)kp * 2 * NB + e, (int16_t)src);
+          C* at = mats + (size_t)(kp * 5 + (e < NB ? 0 : 1)) * BB + (e < NB ? e : e - NB);
+          C v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = gld(scr + ((4 * u + q) * 2 * NB + src));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) gst(at + (4 * u + q) * NB, v[q]);
+        }
+        continue;
+      }
+      u -= ngather;
+      // the other parity's multipliers: zeros, for block k + 1
+      C* scr = lscr + (((kblk + 1) & 1) * 2 * BB + u * 16 * NB);
+      for (int e = lane; e < 16 * NB; e += 64) gst(scr + e, mk<R>(0, 0));
     }
-    __syncthreads();
-    jr = rslot(1);
-    jcs = cslot(1);
-    if (++jj == nb) {
+    // what the waves wrote to global memory is read by others in later steps
+    // of the block where the window is partly there, else not before the next
+    // block
+    if (LT < MT || up)
+      __syncthreads();
+    else
+      lds_barrier();
+    // ---- the next step's state
+    jj += kP;
+    if (o != 0) {
+      if (++jp == NCB) jp = 0;
+      if (++tj == RPB) tj = 0;
+    }
+    if (jj == NB) {
       jj = 0;
-      ++k;
+      ++kblk;
     }
-  };
-  c128 ra[ER], rb[ER];
-  fetch_row(ra, 0);
-  for (int64_t j = 0; j < npad; j += 2) {
-    step(j, ra, rb);
-    if (j + 1 < npad) step(j + 1, rb, ra);
   }
-  if (t == 0 && first_zero) gst(info + s, first_zero);
+  // the last block's multipliers and permutation
+  {
+    const int kp = K - 1, pp = kp & 1;
+    const C* scr = lscr + pp * 2 * BB;
+    for (int c = w - 1; c < NB; c += NW - 1)
+      for (int e = lane; e < 2 * NB; e += 64) {
+        const int src = idx[pp * 2 * NB + e];
+        if (c == 0) gst(permg + (size_t)kp * 2 * NB + e, (int16_t)src);
+        gst(mats + (size_t)(kp * 5 + (e < NB ? 0 : 1)) * BB + c * NB + (e < NB ? e : e - NB),
+            gld(scr + (c * 2 * NB + src)));
+      }
+  }
 }
 
 // In-place inverses of the unit lower Lh11 and the upper U(k,k) of every
@@ -754,29 +1108,44 @@ static int launch_form_qg(cx<R>* mats, int nb, int nblk, hipStream_t st) {
 }
 
 template <typename R>
-static size_t lu_lds_head_bytes(int b) {
-  const int nb = block_size(b);
-  size_t head = (sizeof(int) * (size_t)((b + 2) + 8 * nb + 4) + 15) & ~(size_t)15;
-  return head + sizeof(cx<R>) * ((size_t)b + 1);
-}
-template <typename R>
-static size_t lu_lds_bytes(int b) {
-  return lu_lds_head_bytes<R>(b) + sizeof(cx<R>) * (size_t)(b + 2) * (2 * b + 2);
-}
-
-// whole window rows that fit in LDS beside the head when the window does not
-template <typename R>
-static int lu_lds_rows(int b) {
-  const size_t row = sizeof(cx<R>) * (size_t)(2 * b + 2);
-  const size_t head = lu_lds_head_bytes<R>(b);
-  const size_t rows = head < kLdsBudget ? (kLdsBudget - head) / row : 0;
-  return (int)std::min<size_t>(rows, (size_t)b + 2);
-}
-
-template <typename R>
 size_t lu_window_scratch(int b, int nsys) {
-  if (lu_lds_bytes<R>(b) <= kLdsBudget) return 0;
-  return (size_t)nsys * (b + 2) * (2 * b + 2) * sizeof(cx<R>);
+  size_t per = 0;
+  switch (block_size(b)) {
+    case 16: per = LuShape<R, 16>::SCRATCH; break;
+    case 32: per = LuShape<R, 32>::SCRATCH; break;
+    case 48: per = LuShape<R, 48>::SCRATCH; break;
+    case 64: per = LuShape<R, 64>::SCRATCH; break;
+    case 80: per = LuShape<R, 80>::SCRATCH; break;
+    case 96: per = LuShape<R, 96>::SCRATCH; break;
+    case 112: per = LuShape<R, 112>::SCRATCH; break;
+    case 128: per = LuShape<R, 128>::SCRATCH; break;
+  }
+  return (size_t)nsys * per;
+}
+
+template <typename R, int NB>
+static int launch_band_lu_nb(const LuArgs<R>& a, int nsys, hipStream_t st) {
+  (void)hipFuncSetAttribute((const void*)k_band_lu<R, NB>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
+  (void)hipGetLastError();
+  k_band_lu<R, NB><<<nsys, kLuThreads, LuShape<R, NB>::LDS, st>>>(a);
+  FB_HIP(hipGetLastError());
+  return 0;
+}
+
+template <typename R>
+static int launch_band_lu(const LuArgs<R>& a, int nb, int nsys, hipStream_t st) {
+  switch (nb) {
+    case 16: return launch_band_lu_nb<R, 16>(a, nsys, st);
+    case 32: return launch_band_lu_nb<R, 32>(a, nsys, st);
+    case 48: return launch_band_lu_nb<R, 48>(a, nsys, st);
+    case 64: return launch_band_lu_nb<R, 64>(a, nsys, st);
+    case 80: return launch_band_lu_nb<R, 80>(a, nsys, st);
+    case 96: return launch_band_lu_nb<R, 96>(a, nsys, st);
+    case 112: return launch_band_lu_nb<R, 112>(a, nsys, st);
+    case 128: return launch_band_lu_nb<R, 128>(a, nsys, st);
+    default: return FB_ERR_INTERNAL;
+  }
 }
 
 // Transposed copy of every nb x nb factor block (32 x 32 tiles through LDS),
@@ -815,28 +1184,11 @@ int launch_lu_impl(const Band& bd, int nsys, const c128* z_dev, cx<R>* mats, cx<
   const int b = bd.b;
   const int nb = block_size(b);
   const int K = (int)((bd.n + nb - 1) / nb);
-  FactorOut<R> o{mats, perm, info, lscr};
-  bool lds = lu_lds_bytes<R>(b) <= kLdsBudget;
-  // split window: the leading physical rows that fit stay in LDS
-  const int lrows = lds ? b + 2 : lu_lds_rows<R>(b);
-  const int wsplit = lrows * (2 * b + 2);
-  size_t smem = lds ? lu_lds_bytes<R>(b)
-                    : lu_lds_head_bytes<R>(b) + sizeof(cx<R>) * (size_t)wsplit;
-  if (smem > kLdsBudget) return FB_ERR_INTERNAL;
-  (void)hipFuncSetAttribute((const void*)k_band_lu<R, true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
-  (void)hipFuncSetAttribute((const void*)k_band_lu<R, false>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
-  (void)hipGetLastError();
+  if (bd.Bblk == nullptr || bd.nb != nb) return FB_ERR_INTERNAL;
+  const LuArgs<R> a{bd.Bblk, bd.n, K, z_dev, mats, perm, info, lscr, scratch};
   {
     ProfScope ps(FB_PROF_LU, st, 16.0 * (double)bd.n * b * b * nsys);
-    if (lds)
-      k_band_lu<R, true><<<nsys, kLuThreads, smem, st>>>(bd.Bd, bd.n, b, nb, K, z_dev, o, scratch,
-                                                         wsplit);
-    else
-      k_band_lu<R, false><<<nsys, kLuThreads, smem, st>>>(bd.Bd, bd.n, b, nb, K, z_dev, o, scratch,
-                                                          wsplit);
-    FB_HIP(hipGetLastError());
+    FB_TRY(launch_band_lu<R>(a, nb, nsys, st));
   }
   int nblk = nsys * K;
   // inverses (2 nb^3 / 3 complex multiply-adds per block), M (nb^3 / 2) and

@@ -39,7 +39,7 @@ struct BJDev {  // kBjDescBytes bytes
   c128* U;      // h x 64 x 64, row-major per pair: U[K][k * 64 + j] = U_K(k, j)
   int32_t* skip;// h: U of the pair is the identity
   double* part; // 2 doubles per column of A: off^2 and total^2 partial sums
-  int32_t m, mp, h, cur;
+  int32_t m, mp, h, pad;
 };
 
 typedef double bd4 __attribute__((ext_vector_type(4)));
@@ -78,11 +78,11 @@ __global__ void k_bj_init(const JacobiJob* __restrict__ jobs, BJDev* __restrict_
 
 // -------------------------------------------------------------- off-norm
 // padding columns and rows (diagonal kPad) are left out
-__global__ void __launch_bounds__(256) k_bj_norms(BJDev* __restrict__ dv) {
+__global__ void __launch_bounds__(256) k_bj_norms(BJDev* __restrict__ dv, int cur) {
   const BJDev d = dv[blockIdx.y];
   const int j = blockIdx.x;
   if (j >= d.mp) return;
-  const c128* A = (d.cur ? d.A[1] : d.A[0]);
+  const c128* A = (cur ? d.A[1] : d.A[0]);
   __shared__ double r0[256], r1[256];
   double off = 0.0, all = 0.0;
   const bool padj = gld(A + (int64_t)j * d.mp + j).x > 0.5 * kPad;
@@ -132,39 +132,163 @@ __global__ void k_bj_norms_final(BJDev* __restrict__ dv, int nmat, double* __res
 static constexpr int kInner = 1;
 static constexpr int kPairThreads = 1024;  // one 2 x 2 block update per thread per round
 
-__device__ __forceinline__ int bj_player(int pos, int r, int n) {
-  return pos == 0 ? 0 : 1 + (pos - 1 + r) % (n - 1);
-}
+// Rotation of one pair: columns p, q are turned by J = [cs sn; -e sn  e cs].
+struct alignas(16) BJRot {
+  double cs, sn;
+  c128 e;
+};
+// position's pair in the round: positions k and kPb - 1 - k play each other
+__device__ __forceinline__ int bj_pair(int pos) { return pos < kBs ? pos : kPb - 1 - pos; }
 
-__global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ dv) {
-  extern __shared__ __align__(16) char lds_raw[];
-  c128* S = reinterpret_cast<c128*>(lds_raw);  // column-major, ld kPL
-  c128* Us = S + kPb * kPL;                    // column-major, ld kPL
-  __shared__ double s_cs[kBs], s_sn[kBs];
-  __shared__ c128 s_e[kBs];
-  __shared__ int s_p[kBs], s_q[kBs];
-  __shared__ double red[2][kPairThreads];
-  const BJDev d = dv[blockIdx.y];
-  const int K = blockIdx.x;
-  if (K >= d.h) return;
-  const int t = threadIdx.x;
-  const c128* A = (d.cur ? d.A[1] : d.A[0]);
-  const int64_t base = (int64_t)K * kPb;
-  for (int e = t; e < kPb * kPb; e += blockDim.x) {
+// Elements of the pair problem: complex, or real where no imaginary part is
+// set (a real matrix: the same operations without the terms that are zero).
+template <bool CPLX>
+struct BJElem;
+template <>
+struct BJElem<true> {
+  using E = c128;
+  static __device__ __forceinline__ E from(c128 v) { return v; }
+  static __device__ __forceinline__ c128 to(E v) { return v; }
+  static __device__ __forceinline__ double norm2(E v) { return cabs2(v); }
+  static __device__ __forceinline__ double re(E v) { return v.x; }
+  static __device__ __forceinline__ double im(E v) { return v.y; }
+  // e v (in S and in U: the two round their imaginary parts in another
+  // order), conj(e) v
+  static __device__ __forceinline__ E mul(c128 e, E v) {
+    return mk(fma(e.x, v.x, -(e.y * v.y)), fma(v.y, e.x, v.x * e.y));
+  }
+  static __device__ __forceinline__ E mulu(c128 e, E v) {
+    return mk(fma(e.x, v.x, -(e.y * v.y)), fma(e.y, v.x, v.y * e.x));
+  }
+  static __device__ __forceinline__ E mulc(c128 e, E v) {
+    return mk(fma(e.x, v.x, e.y * v.y), fma(e.x, v.y, -(e.y * v.x)));
+  }
+  // c a - s b, s a + c b
+  static __device__ __forceinline__ E minus(double c, E a, double s, E b) {
+    return mk(fma(c, a.x, -(s * b.x)), fma(c, a.y, -(s * b.y)));
+  }
+  static __device__ __forceinline__ E plus(double s, E a, double c, E b) {
+    return mk(fma(s, a.x, c * b.x), fma(s, a.y, c * b.y));
+  }
+};
+template <>
+struct BJElem<false> {
+  using E = double;
+  static __device__ __forceinline__ E from(c128 v) { return v.x; }
+  static __device__ __forceinline__ c128 to(E v) { return mk(v, 0.0); }
+  static __device__ __forceinline__ double norm2(E v) { return v * v; }
+  static __device__ __forceinline__ double re(E v) { return v; }
+  static __device__ __forceinline__ double im(E) { return 0.0; }
+  static __device__ __forceinline__ E mul(c128 e, E v) { return e.x * v; }
+  static __device__ __forceinline__ E mulu(c128 e, E v) { return e.x * v; }
+  static __device__ __forceinline__ E mulc(c128 e, E v) { return e.x * v; }
+  static __device__ __forceinline__ E minus(double c, E a, double s, E b) {
+    return fma(c, a, -(s * b));
+  }
+  static __device__ __forceinline__ E plus(double s, E a, double c, E b) {
+    return fma(s, a, c * b);
+  }
+};
+
+// A round has one barrier: wave 0 updates the 64 2 x 2 blocks of S that the
+// next round's rotations are formed from (the diagonal ones and, for every
+// next pair, the one that holds its off-diagonal element) and goes on to form
+// them, while the other 15 waves update the 960 blocks left, one per thread,
+// and turn U.
+// What bounds it: the angles' chain of divisions and square roots on one
+// wave, and in complex arithmetic the LDS traffic of S and U beside it.  With
+// all waves waiting for the angles and two barriers a launch of 63 rounds took
+// 147 us, real or complex; now 122 us complex (three matrices of 320 columns)
+// and 87 us real.
+template <bool CPLX>
+__device__ __forceinline__ int bj_pair_sweeps(char* lds, BJRot (*rot)[kBs],
+                                              double (*red)[kPairThreads],
+                                              const c128* __restrict__ A, int64_t base, int mp,
+                                              c128* __restrict__ U) {
+  using X = BJElem<CPLX>;
+  using E = typename X::E;
+  E* S = reinterpret_cast<E*>(lds);  // column-major, ld kPL
+  E* Us = S + kPb * kPL;             // column-major, ld kPL
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  for (int e = t; e < kPb * kPb; e += kPairThreads) {
     const int cj = e / kPb, ci = e % kPb;
-    S[cj * kPL + ci] = gld(A + (base + cj) * d.mp + base + ci);
-    Us[cj * kPL + ci] = mk(ci == cj ? 1.0 : 0.0, 0.0);
+    S[cj * kPL + ci] = X::from(gld(A + (base + cj) * mp + base + ci));
+    Us[cj * kPL + ci] = X::from(mk(ci == cj ? 1.0 : 0.0, 0.0));
   }
   __syncthreads();
+  // the player at position pos in round r, r <= kPb - 2
+  auto player = [](int pos, int r) {
+    int v = pos + r;
+    v = v >= kPb ? v - (kPb - 1) : v;
+    return pos == 0 ? 0 : v;
+  };
+  // rotations of round ro by one wave: lanes k and k + 32 take pair k, the
+  // first its angle, the second its phase
+  auto angles = [&](int ro, BJRot* o) {
+    const int k = lane & 31;
+    const bool second = lane >= 32;
+    const int a = player(k, ro), b = player(kPb - 1 - k, ro);
+    const int p = a < b ? a : b, q = a < b ? b : a;
+    const E c = S[q * kPL + p];
+    const double ac = sqrt(X::norm2(c));
+    const double app = X::re(S[p * kPL + p]), aqq = X::re(S[q * kPL + q]);
+    const bool turn = ac > 1e-300 && ac > 1e-18 * (fabs(app) + fabs(aqq));
+    const double x = (second ? X::re(c) : aqq - app) / (second ? ac : 2.0 * ac);  // tau
+    const double y = (second ? -X::im(c) : x >= 0.0 ? 1.0 : -1.0) /
+                     (second ? ac : fabs(x) + hypot(1.0, x));                     // tan
+    const double cs = 1.0 / sqrt(1.0 + y * y), sn = y * cs;
+    BJRot* at = o + k;
+    if (second)
+      at->e = turn ? mk(x, y) : mk(1.0, 0.0);  // e^{-i arg c}
+    else
+      *reinterpret_cast<c128*>(at) = turn ? mk(cs, sn) : mk(1.0, 0.0);
+  };
+  // S <- J^H S J on one 2 x 2 block: rows of pair kk, columns of pair ll
+  auto block = [&](const BJRot* o, int ro, int kk, int ll) {
+    const int ak = player(kk, ro), bk = player(kPb - 1 - kk, ro);
+    const int al = player(ll, ro), bl = player(kPb - 1 - ll, ro);
+    const int pk = min(ak, bk), qk = max(ak, bk), pl = min(al, bl), ql = max(al, bl);
+    const BJRot rk = o[kk], rl = o[ll];
+    const E a00 = S[pl * kPL + pk], a10 = S[pl * kPL + qk];
+    const E a01 = X::mul(rl.e, S[ql * kPL + pk]), a11 = X::mul(rl.e, S[ql * kPL + qk]);
+    const E b00 = X::minus(rl.cs, a00, rl.sn, a01), b01 = X::plus(rl.sn, a00, rl.cs, a01);
+    const E b10 = X::mulc(rk.e, X::minus(rl.cs, a10, rl.sn, a11));
+    const E b11 = X::mulc(rk.e, X::plus(rl.sn, a10, rl.cs, a11));
+    S[pl * kPL + pk] = X::minus(rk.cs, b00, rk.sn, b10);
+    S[pl * kPL + qk] = X::plus(rk.sn, b00, rk.cs, b10);
+    S[ql * kPL + pk] = X::minus(rk.cs, b01, rk.sn, b11);
+    S[ql * kPL + qk] = X::plus(rk.sn, b01, rk.cs, b11);
+  };
+  // Pair j of the next round is made of the players at positions j + 1 and
+  // kPb - j (0 and 1 for j = 0), which play in pairs xj and yj of this one:
+  // every pair k meets two others, k - 2 and k + 2 (0 also 1, kBs - 1 also
+  // kBs - 2).  Threads of wave 0 from 32 on take the block whose row holds the
+  // lower player, the last 32 threads its mirror image; the other threads take
+  // the remaining off-diagonal blocks, 29 to a pair ll.
+  const int g = t - 64, j = w == 0 ? lane & 31 : g - 29 * kBs;
+  const bool meet = w == 0 ? lane >= 32 : j >= 0;
+  const int posx = j == 0 ? 0 : j + 1, posy = j == 0 ? 1 : kPb - j;
+  int kk = lane & 31, ll = kk;
+  if (w != 0 && !meet) {
+    ll = g / 29;
+    const int e0 = ll == 1 ? 0 : ll == 0 ? 0 : ll - 2;
+    const int e1 = ll == 0 ? 1 : ll == 1 ? 1 : ll == kBs - 1 ? kBs - 2 : ll;
+    const int e2 = ll == 0 ? 2 : ll == 1 ? 3 : ll >= kBs - 2 ? kBs - 1 : ll + 2;
+    kk = g - 29 * ll;
+    kk += kk >= e0 ? 1 : 0;
+    kk += kk >= e1 ? 1 : 0;
+    kk += kk >= e2 ? 1 : 0;
+  }
   int rotated = 0;
   for (int sw = 0; sw < kInner; ++sw) {
     // stop when the block is diagonal relative to its (non-padding) diagonal
     double off = 0.0, dg = 0.0;
-    for (int e = t; e < kPb * kPb; e += blockDim.x) {
+    for (int e = t; e < kPb * kPb; e += kPairThreads) {
       const int cj = e / kPb, ci = e % kPb;
-      const c128 v = S[cj * kPL + ci];
-      if (ci != cj) off += cabs2(v);
-      else dg += fabs(v.x) < 0.5 * kPad ? cabs2(v) : 0.0;
+      const E v = S[cj * kPL + ci];
+      if (ci != cj) off += X::norm2(v);
+      else dg += fabs(X::re(v)) < 0.5 * kPad ? X::norm2(v) : 0.0;
     }
     red[0][t] = off;
     red[1][t] = dg;
@@ -180,64 +304,60 @@ __global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ d
     __syncthreads();
     if (diag) break;  // uniform: every thread read the same sums
     rotated = 1;
+    if (w == 0) angles(0, rot[0]);
+    __syncthreads();
     for (int ro = 0; ro < kPb - 1; ++ro) {
-      if (t < kBs) {
-        const int a = bj_player(t, ro, kPb), b = bj_player(kPb - 1 - t, ro, kPb);
-        const int p = a < b ? a : b, q = a < b ? b : a;
-        s_p[t] = p;
-        s_q[t] = q;
-        double cs = 1.0, sn = 0.0;
-        c128 e = mk(1.0, 0.0);
-        const c128 c = S[q * kPL + p];
-        const double ac = sqrt(cabs2(c));
-        const double app = S[p * kPL + p].x, aqq = S[q * kPL + q].x;
-        if (ac > 1e-300 && ac > 1e-18 * (fabs(app) + fabs(aqq))) {
-          const double tau = (aqq - app) / (2.0 * ac);
-          const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + hypot(1.0, tau));
-          cs = 1.0 / sqrt(1.0 + tt * tt);
-          sn = tt * cs;
-          e = mk(c.x / ac, -c.y / ac);  // e^{-i arg c}
+      const BJRot* o = rot[ro & 1];
+      if (meet) {
+        const int x = bj_pair(posx), y = bj_pair(posy);
+        const bool low = (player(posx, ro) < player(posy, ro)) == (w == 0);
+        kk = low ? x : y;
+        ll = low ? y : x;
+      }
+      block(o, ro, kk, ll);
+      if (w == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (ro + 2 < kPb) angles(ro + 1, rot[(ro & 1) ^ 1]);
+      } else {
+        // U <- U J (columns p, q), a pair per wave
+        for (int k = w - 1; k < kBs; k += kPairThreads / 64 - 1) {
+          const int a = player(k, ro), b = player(kPb - 1 - k, ro);
+          const int p = min(a, b), q = max(a, b);
+          const BJRot r = o[k];
+          const E vp = Us[p * kPL + lane], vq = X::mulu(r.e, Us[q * kPL + lane]);
+          Us[p * kPL + lane] = X::minus(r.cs, vp, r.sn, vq);
+          Us[q * kPL + lane] = X::plus(r.sn, vp, r.cs, vq);
         }
-        s_cs[t] = cs;
-        s_sn[t] = sn;
-        s_e[t] = e;
-      }
-      __syncthreads();
-      // S <- J^H S J by 2 x 2 blocks (pair kk rows, pair ll columns)
-      for (int e2 = t; e2 < kBs * kBs; e2 += blockDim.x) {
-        const int kk = e2 % kBs, ll = e2 / kBs;
-        const int pk = s_p[kk], qk = s_q[kk], pl = s_p[ll], ql = s_q[ll];
-        const c128 a00 = S[pl * kPL + pk], a10 = S[pl * kPL + qk];
-        const c128 a01 = S[ql * kPL + pk], a11 = S[ql * kPL + qk];
-        const double cl = s_cs[ll], sl = s_sn[ll];
-        const c128 el = s_e[ll];
-        const c128 b00 = cl * a00 - sl * (el * a01), b01 = sl * a00 + cl * (el * a01);
-        const c128 b10 = cl * a10 - sl * (el * a11), b11 = sl * a10 + cl * (el * a11);
-        const double ck = s_cs[kk], sk = s_sn[kk];
-        const c128 ek = cconj(s_e[kk]);
-        S[pl * kPL + pk] = ck * b00 - sk * (ek * b10);
-        S[pl * kPL + qk] = sk * b00 + ck * (ek * b10);
-        S[ql * kPL + pk] = ck * b01 - sk * (ek * b11);
-        S[ql * kPL + qk] = sk * b01 + ck * (ek * b11);
-      }
-      // U <- U J (columns p, q)
-      for (int e2 = t; e2 < kBs * kPb; e2 += blockDim.x) {
-        const int kk = e2 / kPb, i = e2 % kPb;
-        const int p = s_p[kk], q = s_q[kk];
-        const double cs = s_cs[kk], sn = s_sn[kk];
-        const c128 e = s_e[kk];
-        const c128 vp = Us[p * kPL + i], vq = Us[q * kPL + i];
-        Us[p * kPL + i] = cs * vp - sn * (e * vq);
-        Us[q * kPL + i] = sn * vp + cs * (e * vq);
       }
       __syncthreads();
     }
   }
-  c128* U = d.U + (size_t)K * kPb * kPb;
-  for (int e = t; e < kPb * kPb; e += blockDim.x) {
-    const int k = e / kPb, j = e % kPb;  // row-major
-    gst(U + e, Us[j * kPL + k]);
+  for (int e = t; e < kPb * kPb; e += kPairThreads) {
+    const int k = e / kPb, jc = e % kPb;  // row-major
+    gst(U + e, X::to(Us[jc * kPL + k]));
   }
+  return rotated;
+}
+
+__global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ dv, int cur) {
+  extern __shared__ __align__(16) char lds_raw[];
+  __shared__ BJRot rot[2][kBs];
+  __shared__ double red[2][kPairThreads];
+  const BJDev d = dv[blockIdx.y];
+  const int K = blockIdx.x;
+  if (K >= d.h) return;
+  const int t = threadIdx.x;
+  const c128* A = (cur ? d.A[1] : d.A[0]);
+  const int64_t base = (int64_t)K * kPb;
+  bool imag = false;
+  for (int e = t; e < kPb * kPb; e += kPairThreads)
+    imag |= gld(A + (base + e / kPb) * d.mp + base + e % kPb).y != 0.0;
+  c128* U = d.U + (size_t)K * kPb * kPb;
+  const int rotated = __syncthreads_or(imag)
+                          ? bj_pair_sweeps<true>(lds_raw, rot, red, A, base, d.mp, U)
+                          : bj_pair_sweeps<false>(lds_raw, rot, red, A, base, d.mp, U);
   if (t == 0) gst(d.skip + K, rotated ? 0 : 1);
 }
 
@@ -295,7 +415,7 @@ __device__ __forceinline__ void bj_quarter(bd4 (&p1)[2][2], bd4 (&p2)[2][2], bd4
   }
 }
 
-__global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv) {
+__global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv, int cur) {
   extern __shared__ __align__(16) char lds_raw[];
   c128* Ts = reinterpret_cast<c128*>(lds_raw);  // 64 x 64, column-major, ld kPL
   const BJDev d = dv[blockIdx.y];
@@ -317,7 +437,6 @@ __global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv) {
     K = (wg - nA) / h;  // row tile of V
     L = (wg - nA) % h;
   }
-  const int cur = d.cur;
   // (selects, not indexing: an indexed member array would live in scratch)
   const c128* Src = isA ? (cur ? d.A[1] : d.A[0]) : (cur ? d.V[1] : d.V[0]);
   c128* Dst = isA ? (cur ? d.A[0] : d.A[1]) : (cur ? d.V[0] : d.V[1]);
@@ -385,10 +504,10 @@ __global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv) {
 // -------------------------------------------------------------- results
 // eigenvalues ascending (rank by value, ties by position; the padding ranks
 // last) and the matching columns of V (first m rows) into the job's outputs
-__global__ void k_bj_rank(const JacobiJob* __restrict__ jobs, BJDev* __restrict__ dv) {
+__global__ void k_bj_rank(const JacobiJob* __restrict__ jobs, BJDev* __restrict__ dv, int cur) {
   const JacobiJob jb = jobs[blockIdx.y];
   const BJDev d = dv[blockIdx.y];
-  const c128* A = (d.cur ? d.A[1] : d.A[0]);
+  const c128* A = (cur ? d.A[1] : d.A[0]);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= d.mp) return;
   const double wi = gld(A + (int64_t)i * d.mp + i).x;
@@ -403,10 +522,11 @@ __global__ void k_bj_rank(const JacobiJob* __restrict__ jobs, BJDev* __restrict_
   }
 }
 
-__global__ void k_bj_vectors(const JacobiJob* __restrict__ jobs, BJDev* __restrict__ dv) {
+__global__ void k_bj_vectors(const JacobiJob* __restrict__ jobs, BJDev* __restrict__ dv,
+                             int cur) {
   const JacobiJob jb = jobs[blockIdx.y];
   const BJDev d = dv[blockIdx.y];
-  const c128* V = (d.cur ? d.V[1] : d.V[0]);
+  const c128* V = (cur ? d.V[1] : d.V[0]);
   const int64_t tot = (int64_t)d.m * d.m;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -414,11 +534,6 @@ __global__ void k_bj_vectors(const JacobiJob* __restrict__ jobs, BJDev* __restri
     const int src = gld(jb.order + k);
     gst(jb.W + (int64_t)k * jb.ldw + i, gld(V + (int64_t)src * d.mp + i));
   }
-}
-
-__global__ void k_bj_flip(BJDev* __restrict__ dv, int nmat) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < nmat) dv[q].cur ^= 1;
 }
 
 // -------------------------------------------------------------- driver
@@ -443,7 +558,7 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
     d.m = jobs[q].m;
     d.h = bj_h(d.m);
     d.mp = kPb * d.h;
-    d.cur = 0;
+    d.pad = 0;
     auto take = [&](size_t bytes) {
       char* p = work + off;
       off += (bytes + 255) & ~(size_t)255;
@@ -477,10 +592,10 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   k_bj_init<<<dim3(1024, nj), 256, 0, st>>>(jobs_dev, dvd);
   FB_HIP(hipGetLastError());
   std::vector<double> nrm(2 * nj);
-  int sweeps = 0;
+  int sweeps = 0, cur = 0;  // cur: which copy of A and V a round reads
   const int upd_wgs = max_h * (max_h + 1) / 2 + max_h * (max_mp / kPb);
   for (int sw = 0; sw <= max_sweeps; ++sw) {
-    k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd);
+    k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd, cur);
     FB_HIP(hipGetLastError());
     k_bj_norms_final<<<(nj + 63) / 64, 64, 0, st>>>(dvd, nj, norms_dev);
     FB_HIP(hipGetLastError());
@@ -494,17 +609,16 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
     // every matrix takes max_rounds rounds (a smaller one completes further
     // sweeps of its own schedule, which keeps it converging)
     for (int r = 0; r < max_rounds; ++r) {
-      k_bj_pairs<<<dim3(max_h, nj), kPairThreads, lds_pairs, st>>>(dvd);
+      k_bj_pairs<<<dim3(max_h, nj), kPairThreads, lds_pairs, st>>>(dvd, cur);
       FB_HIP(hipGetLastError());
-      k_bj_update<<<dim3(upd_wgs, nj), 256, lds_upd, st>>>(dvd);
+      k_bj_update<<<dim3(upd_wgs, nj), 256, lds_upd, st>>>(dvd, cur);
       FB_HIP(hipGetLastError());
-      k_bj_flip<<<(nj + 63) / 64, 64, 0, st>>>(dvd, nj);
-      FB_HIP(hipGetLastError());
+      cur ^= 1;
     }
   }
-  k_bj_rank<<<dim3((max_mp + 255) / 256, nj), 256, 0, st>>>(jobs_dev, dvd);
+  k_bj_rank<<<dim3((max_mp + 255) / 256, nj), 256, 0, st>>>(jobs_dev, dvd, cur);
   FB_HIP(hipGetLastError());
-  k_bj_vectors<<<dim3(1024, nj), 256, 0, st>>>(jobs_dev, dvd);
+  k_bj_vectors<<<dim3(1024, nj), 256, 0, st>>>(jobs_dev, dvd, cur);
   FB_HIP(hipGetLastError());
   for (int q = 0; q < nj; ++q)
     if (jobs[q].sweeps) FB_HIP(hipMemcpyAsync(jobs[q].sweeps, &sweeps, sizeof(int32_t),

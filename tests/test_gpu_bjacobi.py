@@ -1,0 +1,44 @@
+"""The pair problems of the parallel block Jacobi, real and complex: a reduced
+matrix whose pairs are all real, all complex, or some of each (a basis on two
+decoupled halves of the matrix, the first one real).  Oracle: LAPACK's
+eigenvalues of the same reduced matrix.  Tolerance: two-sided Jacobi and LAPACK
+are both backward stable, and the reduced matrix is formed twice (n eps
+||B|| each), so the Ritz values agree to well within 1e-12 ||B||_1; the vectors
+are orthonormal to m eps times a modest factor, below 1e-12."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import band as oband
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["real", "complex", "mixed"])
+@pytest.mark.parametrize("m", [257, 320, 385])
+def test_pairs_real_and_complex(kind, m):
+    import paper_2012_00506_amd as fb
+    n, b, h = 900, 6, 450
+    print(f"bjacobi kind={kind} m={m}", flush=True)
+    ab = synth.band_matrix(n, b, 31, kind != "real", -20, 20)
+    rng = np.random.default_rng(m)
+    Q = rng.standard_normal((n, m))
+    if kind != "real":
+        Q = Q + 1j * rng.standard_normal((n, m))
+    if kind == "mixed":
+        ab[:, :h] = ab[:, :h].real
+        for d in range(1, b + 1):
+            ab[d, h - d:h] = 0.0  # the halves are decoupled
+        k = m // 2
+        Q[:h, :k] = Q[:h, :k].real
+        Q[h:, :k] = 0.0
+        Q[:h, k:] = 0.0
+    Q, _ = np.linalg.qr(Q)
+    r = fb.rayleigh_ritz(ab, [fb.to_colmajor(Q)])[0]
+    A = Q.conj().T @ oband.dense_from_band(ab) @ Q
+    lam = np.linalg.eigvalsh((A + A.conj().T) / 2)
+    nrm = oband.norm1(ab)
+    assert r.rank == m
+    assert np.abs(np.sort(r.lam) - lam).max() <= 1e-12 * nrm
+    X = r.X.cpu().numpy()
+    assert np.abs(X.conj().T @ X - np.eye(m)).max() < 1e-12

@@ -394,7 +394,7 @@ int fb_profile_enable(int32_t on);
 int fb_profile_read(int32_t cls, int64_t* launches, double* ms, double* work);
 
 /* Autotuner of the block-solve kernel (the tile width of right-hand sides per
- * work item and whether factor fragments are prefetched a product ahead):
+ * work item; without it a rule on the sizes of the call chooses):
  * factors nsys shifted systems of B in the given precision (0: complex128,
  * 1: complex64), times every variant that fits in LDS on the N and H solves
  * of m right-hand sides each with HIP events, and keeps the fastest for this

@@ -557,7 +557,7 @@ void carve_feast(Arena& ar, const Band& bd, int W, int maxm, int ne, bool ir, in
   carve_eig_work(ar, std::vector<int>(W, maxm), fb.ew);
   fb.perm_dev = ar.take<int32_t>(maxm);
   fb.acc_dev = ar.take<AccJob>(W);
-  fb.tile = solve_tile<R>(bd.b);
+  fb.tile = solve_tile<R>(bd.b, (size_t)W * ((maxm + 31) / 32) * P);
   const int max_jobs = W * ((maxm + fb.tile - 1) / fb.tile);
   fb.P = P;
   fb.Xp.assign((size_t)W * P, nullptr);
@@ -1075,14 +1075,16 @@ int filter_impl(const fb_band* B, int nslice, const double* lo, const double* hi
     }
   }
   AccJob* acc_dev = ar.take<AccJob>(nslice);
-  const int tile = solve_tile<R>(bd.b);
+  const int npair = ne * (cplx ? 2 : 1);
+  size_t tiles32 = 0;
+  for (int i = 0; i < nslice; ++i) tiles32 += (size_t)((m[i] + 31) / 32) * npair;
+  const int tile = solve_tile<R>(bd.b, tiles32);
   int max_jobs = 0;
   size_t cols = 0;
   for (int i = 0; i < nslice; ++i) {
     max_jobs += (m[i] + tile - 1) / tile;
     cols += std::max(m[i], 1);
   }
-  const int npair = ne * (cplx ? 2 : 1);
   const int P = pairs_per_launch(o->hbm_budget, o->pairs, o->batched != 0, npair,
                                  ar.used + refine_bytes(bd, tile, max_jobs, ir, need_res),
                                  (size_t)n * cols * sizeof(c128));

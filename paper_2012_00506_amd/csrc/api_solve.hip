@@ -282,7 +282,7 @@ template <typename R>
 int refine_launch(const Band& bd, const cx<R>* mats, const cx<R>* matsT, const int16_t* perm,
                   const RefinePlan& plan, RefineBufs& rb, hipStream_t st) {
   if (plan.njobs == 0) return 0;
-  FB_TRY(launch_solve_jobs<R>(mats, matsT, perm, bd.n, bd.b, plan.njobs, rb.jobs_dev,
+  FB_TRY(launch_solve_jobs<R>(mats, matsT, perm, bd.n, bd.b, rb.tile, plan.njobs, rb.jobs_dev,
                               solve_flops(bd.n, bd.b, plan.cols), st));
   if (!plan.need_res) return 0;
   for (size_t w0 = 0, wi = 0; w0 < (size_t)plan.ng; w0 += rb.wave, ++wi) {
@@ -295,7 +295,7 @@ int refine_launch(const Band& bd, const cx<R>* mats, const cx<R>* matsT, const i
                                 resid_flops(bd.n, bd.b, wcols), st));
     for (int pass = 1; pass <= plan.maxpass; ++pass) {
       // gated launches: their work is added once the passes are known
-      FB_TRY(launch_solve_jobs<R>(mats, matsT, perm, bd.n, bd.b,
+      FB_TRY(launch_solve_jobs<R>(mats, matsT, perm, bd.n, bd.b, rb.tile,
                                   (int)(plan.cj_off[wi + 1] - plan.cj_off[wi]),
                                   rb.cjobs_dev + plan.cj_off[wi], 0.0, st, rb.flag));
       ctl.gate = rb.flag;
@@ -497,7 +497,10 @@ int shifted_solve_impl(const fb_band* B, int nsys, const double* z, const int32_
   }
 
   // jobs: every (system, direction, tile)
-  const int tile = solve_tile<R>(bd.b);
+  size_t tiles32 = 0;
+  for (int s = 0; s < nsys; ++s)
+    tiles32 += (size_t)((m[s] + 31) / 32) * ((X[s] != nullptr) + (XH && XH[s]));
+  const int tile = solve_tile<R>(bd.b, tiles32);
   std::vector<SolveJob> jobs;
   for (int s = 0; s < nsys; ++s)
     for (int dir = 0; dir < 2; ++dir) {

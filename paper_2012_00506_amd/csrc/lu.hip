@@ -21,9 +21,9 @@
 // Within a block the multipliers are written to a per-system scratch under
 // their row's position at the block's start (or entry), and gathered into row
 // order once after the end of the block.
+#include "mfma.h"
 #include "prof.h"
 #include "solve_job.h"
-#include "solve_kernel.h"
 
 namespace fb {
 
@@ -60,6 +60,87 @@ __device__ __forceinline__ uint32_t high_bits(double v) {
 __device__ __forceinline__ uint32_t low_bits(float) { return 0; }
 __device__ __forceinline__ uint32_t low_bits(double v) {
   return (uint32_t)__double_as_longlong(v);
+}
+
+// ---------------------------------------------------------------- fragments
+// A fragments of one wave for one block product: register s holds
+// A[16 w + lane % 16][4 s + lane / 16] (complex).
+template <typename R, int NB>
+struct Frag {
+  cx<R> a[NB / 4];
+};
+
+// k ranges [k0, k1) are multiples of 16 and the same for the whole wave
+// (readfirstlane makes that visible to the compiler, so that the range test
+// is one scalar branch per 16-row chunk and a chunk's LDS reads issue
+// together).
+template <typename R, int NB>
+__device__ __forceinline__ void frag_load(Frag<R, NB>& f, const cx<R>* A, int w, int lane, int k0,
+                                          int k1) {
+  const int i = 16 * w + (lane & 15), kq = lane >> 4;
+  const int c0 = __builtin_amdgcn_readfirstlane(k0) >> 4;
+  const int c1 = __builtin_amdgcn_readfirstlane(k1) >> 4;
+#pragma unroll
+  for (int ch = 0; ch < NB / 16; ++ch) {
+    if (ch < c0 || ch >= c1) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * ch + 4 * q + kq;
+      f.a[4 * ch + q] = A[(size_t)k * NB + i];
+    }
+  }
+}
+
+// acc += A * B over k in [k0, k1) from prefetched fragments; NEG subtracts.
+// B row k is LDS row k, row stride ldb elements.
+template <typename R, int NB, int NC, bool NEG>
+__device__ __forceinline__ void frag_mma(Acc<R, NC>& acc, const Frag<R, NB>& f, const cx<R>* Bl,
+                                         int ldb, int lane, int k0, int k1) {
+  const int kq = lane >> 4;
+  const int j = lane & 15;
+  const int c0 = __builtin_amdgcn_readfirstlane(k0) >> 4;
+  const int c1 = __builtin_amdgcn_readfirstlane(k1) >> 4;
+#pragma unroll
+  for (int ch = 0; ch < NB / 16; ++ch) {
+    if (ch < c0 || ch >= c1) continue;
+    cx<R> bv[4][NC];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * ch + 4 * q + kq;
+      const cx<R>* bp = Bl + (size_t)k * ldb + j;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) bv[q][c] = bp[16 * c];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      cx<R> a = f.a[4 * ch + q];
+      R ar = a.x, ai = a.y;
+      if (NEG) {
+        ar = -ar;
+        ai = -ai;
+      }
+      const R as = ar + ai;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        acc.p1[c] = MF<R>::mma(ar, bv[q][c].x, acc.p1[c]);
+        acc.p2[c] = MF<R>::mma(ai, bv[q][c].y, acc.p2[c]);
+        acc.p3[c] = MF<R>::mma(as, bv[q][c].x + bv[q][c].y, acc.p3[c]);
+      }
+    }
+  }
+}
+
+// accumulator -> LDS (rows 16 w + MF<R>::row(lane, r), columns 16 c + lane%16)
+template <typename R, int NC>
+__device__ __forceinline__ void acc_to_lds(const Acc<R, NC>& acc, cx<R>* L, int ldb, int w,
+                                           int lane) {
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * w + MF<R>::row(lane, r);
+      L[(size_t)row * ldb + 16 * c + (lane & 15)] = acc.get(c, r);
+    }
 }
 
 // ---------------------------------------------------------------- elimination
@@ -885,19 +966,19 @@ k_block_invert_mfma(cx<R>* __restrict__ mats, int nblk) {
     const int k0 = which == 0 ? 16 * j : 16 * (i + 1);
     const int k1 = which == 0 ? 16 * i : 16 * (j + 1);
     Frag<R, NB> f;
-    frag_load<R, NB, false>(f, (const cx<R>*)M, i, lane, k0, k1);
+    frag_load<R, NB>(f, M, i, lane, k0, k1);
     Acc<R, 1> acc;
     acc.zero();
-    frag_mma<R, NB, 1, false, false>(acc, f, X, LDT, nullptr, 0, lane, k0, k1);
-    acc_to_lds(acc, X, LDT, nullptr, i, 0, lane);  // the sum, at rows 16 i ..
+    frag_mma<R, NB, 1, false>(acc, f, X, LDT, lane, k0, k1);
+    acc_to_lds(acc, X, LDT, i, lane);  // the sum, at rows 16 i ..
     wfence();
     Frag<R, 16> fd;
     dinv_frag(fd, i);
     Acc<R, 1> acc2;
     acc2.zero();
-    frag_mma<R, 16, 1, false, true>(acc2, fd, X + 16 * i * LDT, LDT, nullptr, 0, lane, 0, 16);
+    frag_mma<R, 16, 1, true>(acc2, fd, X + 16 * i * LDT, LDT, lane, 0, 16);
     wfence();
-    acc_to_lds(acc2, X, LDT, nullptr, i, 0, lane);
+    acc_to_lds(acc2, X, LDT, i, lane);
     wfence();
   }
   __syncthreads();  // every wave has read M
@@ -965,7 +1046,7 @@ k_form_m(cx<R>* __restrict__ mats, int nblk) {
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   Frag<R, NB> f;
-  frag_load<R, NB, false>(f, L21, w, lane, 0, NB);
+  frag_load<R, NB>(f, L21, w, lane, 0, NB);
   for (int p0 = 0; p0 < NB; p0 += PW) {
     __syncthreads();
     // the last panel of a block that PW does not divide is partial: its
@@ -977,7 +1058,7 @@ k_form_m(cx<R>* __restrict__ mats, int nblk) {
     __syncthreads();
     Acc<R, NC> acc;
     acc.zero();
-    frag_mma<R, NB, NC, false, false>(acc, f, Lp, LD, nullptr, 0, lane, p0, NB);
+    frag_mma<R, NB, NC, false>(acc, f, Lp, LD, lane, p0, NB);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -1044,7 +1125,7 @@ k_form_qg(cx<R>* __restrict__ mats, int nblk) {
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   Frag<R, NB> f;
-  frag_load<R, NB, false>(f, Ui, w, lane, 16 * w, NB);
+  frag_load<R, NB>(f, Ui, w, lane, 16 * w, NB);
   {
     // fragment s holds row 16 w + lane % 16, column 4 s + lane / 16
     const int i = 16 * w + (lane & 15);
@@ -1067,7 +1148,7 @@ k_form_qg(cx<R>* __restrict__ mats, int nblk) {
       __syncthreads();
       Acc<R, NC> acc;
       acc.zero();
-      frag_mma<R, NB, NC, false, false>(acc, f, Bp, LD, nullptr, 0, lane, 16 * w, NB);
+      frag_mma<R, NB, NC, false>(acc, f, Bp, LD, lane, 16 * w, NB);
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll

@@ -24,38 +24,49 @@
 
 namespace fb {
 // the kernels live in solve_f32.hip / solve_f64.hip
-extern template int launch_variant<float>(int, const c64*, const c64*, const int16_t*, int64_t,
-                                          int, int, const SolveJob*, hipStream_t, const int32_t*);
-extern template int launch_variant<double>(int, const c128*, const c128*, const int16_t*, int64_t,
-                                           int, int, const SolveJob*, hipStream_t, const int32_t*);
+extern template int launch_tiles<float>(int, const c64*, const c64*, const int16_t*, int64_t, int,
+                                        int, const SolveJob*, hipStream_t, const int32_t*);
+extern template int launch_tiles<double>(int, const c128*, const c128*, const int16_t*, int64_t,
+                                         int, int, const SolveJob*, hipStream_t, const int32_t*);
 }  // namespace fb
 
 namespace fb {
 
 // ---------------------------------------------------------------- dispatch
+// Tile width of one call's solves: the autotuner's choice where there is one,
+// else 32 columns in complex64 and 16 in complex128 (a 32-column tile's
+// registers spill there: n = 16384, b = 64, 24 systems x 1056 columns 30.4
+// against 27.7 ms).  Each factor fragment serves twice the columns in a wide
+// tile, but a call with fewer wide tiles than CUs is bound by the length of a
+// tile's sweeps, which are shorter in a narrow one: complex64, n = 16384,
+// b = 64, 16 system-directions of 200, 400 and 800 columns took 1.9, 2.7 and
+// 5.0 ms in 16-column tiles against 2.6, 2.8 and 4.3 ms.
 template <typename R>
-int solve_tile(int b) {
-  return variant_tile(tuned_variant(sizeof(R), block_size(b)));
+int solve_tile(int b, size_t tiles32) {
+  const int nb = block_size(b);
+  const int v = tuned_variant(sizeof(R), nb);
+  if (v >= 0) return variant_tile(v);
+  constexpr size_t kCUs = 256;
+  return sizeof(R) == 4 && tiles32 >= kCUs && variant_fits(sizeof(R), nb, 2) ? 32 : 16;
 }
 
 template <typename R>
 int launch_solve_jobs(const cx<R>* mats, const cx<R>* matsT, const int16_t* perm, int64_t n,
-                      int b, int njobs, const SolveJob* jobs_dev, double work, hipStream_t st,
-                      const int32_t* gate) {
+                      int b, int tile, int njobs, const SolveJob* jobs_dev, double work,
+                      hipStream_t st, const int32_t* gate) {
   if (njobs <= 0) return 0;
   if (sizeof(R) == 4 && matsT == nullptr) return FB_ERR_INTERNAL;
   ProfScope ps(FB_PROF_SOLVE, st, work);
-  const int nb = block_size(b);
-  return launch_variant<R>(tuned_variant(sizeof(R), nb), mats, matsT, perm, n, nb, njobs,
-                           jobs_dev, st, gate);
+  return launch_tiles<R>(tile, mats, matsT, perm, n, block_size(b), njobs, jobs_dev, st, gate);
 }
 
 template int launch_solve_jobs<float>(const c64*, const c64*, const int16_t*, int64_t, int, int,
-                                      const SolveJob*, double, hipStream_t, const int32_t*);
+                                      int, const SolveJob*, double, hipStream_t, const int32_t*);
 template int launch_solve_jobs<double>(const c128*, const c128*, const int16_t*, int64_t, int,
-                                       int, const SolveJob*, double, hipStream_t, const int32_t*);
-template int solve_tile<float>(int);
-template int solve_tile<double>(int);
+                                       int, int, const SolveJob*, double, hipStream_t,
+                                       const int32_t*);
+template int solve_tile<float>(int, size_t);
+template int solve_tile<double>(int, size_t);
 
 // ---------------------------------------------------------------- residual
 // r = y - (zz x - B x) in FP64 for the columns of a job (zz = z for A x = y,

@@ -41,16 +41,17 @@ inline int block_size(int b) { return (b + 15) / 16 * 16; }
 // gate (dev, may be null): a job runs only while gate[job.grp] != 0
 template <typename R>
 int launch_solve_jobs(const cx<R>* mats, const cx<R>* matsT, const int16_t* perm, int64_t n,
-                      int b, int njobs, const SolveJob* jobs_dev, double work, hipStream_t st,
-                      const int32_t* gate = nullptr);
+                      int b, int tile, int njobs, const SolveJob* jobs_dev, double work,
+                      hipStream_t st, const int32_t* gate = nullptr);
 template <typename R>
 int launch_lu_impl(const Band& bd, int nsys, const c128* z_dev, cx<R>* mats, cx<R>* matsT,
                    int16_t* perm, int32_t* info, cx<R>* scratch, cx<R>* lscr, hipStream_t st);
 template <typename R>
 size_t lu_window_scratch(int b, int nsys);
 
+// columns per job of a call with up to tiles32 tiles of 32 columns per launch
 template <typename R>
-int solve_tile(int b);
+int solve_tile(int b, size_t tiles32);
 
 size_t residual_part_doubles(int64_t n, int njobs);
 // columns per residual job for block size nb

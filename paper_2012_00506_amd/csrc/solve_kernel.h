@@ -2,171 +2,12 @@
 // solve_f32.hip and solve_f64.hip).
 #pragma once
 #include "fb_internal.h"
+#include "mfma.h"
 #include "prof.h"
 #include "solve_job.h"
 #include "tune.h"
 
 namespace fb {
-
-// ---------------------------------------------------------------- MFMA helpers
-// One wave computes a 16-row block of a complex product C (16 x T) +=
-// A (16 x K rows of an NB x NB block) * B (K x T, in LDS), as three real
-// 16x16x4 MFMAs per complex one (Gauss form, see Acc).  Lane l feeds
-// A[l % 16][k + l / 16] and B[k + l / 16][l % 16].  Register r of lane l
-// holds C[row][l % 16] with row = 4 (l / 16) + r for the f32 instruction and
-// row = l / 16 + 4 r for the f64 one (both checked on gfx950).
-typedef float mf_f4 __attribute__((ext_vector_type(4)));
-typedef double mf_d4 __attribute__((ext_vector_type(4)));
-
-template <typename R>
-struct MF;
-template <>
-struct MF<float> {
-  using V = mf_f4;
-  static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
-  static __device__ __forceinline__ V mma(float a, float b, V c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct MF<double> {
-  using V = mf_d4;
-  static __device__ __forceinline__ int row(int lane, int r) { return (lane >> 4) + 4 * r; }
-  static __device__ __forceinline__ V mma(double a, double b, V c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-};
-
-// Complex accumulator of NC 16 x 16 tiles in Gauss form: the value is
-// (p1 - p2) + i (p3 - p1 - p2), so that a complex product takes three real
-// MFMA products (p1 += Ar Br, p2 += Ai Bi, p3 += (Ar + Ai)(Br + Bi)).
-template <typename R, int NC>
-struct Acc {
-  typename MF<R>::V p1[NC], p2[NC], p3[NC];
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        p1[c][r] = (R)0;
-        p2[c][r] = (R)0;
-        p3[c][r] = (R)0;
-      }
-  }
-  __device__ __forceinline__ cx<R> get(int c, int r) const {
-    return mk<R>(p1[c][r] - p2[c][r], p3[c][r] - p1[c][r] - p2[c][r]);
-  }
-  __device__ __forceinline__ void set(int c, int r, cx<R> v) {
-    p1[c][r] = v.x;
-    p2[c][r] = (R)0;
-    p3[c][r] = v.x + v.y;
-  }
-};
-
-// A fragments of one wave for one block product: register s holds
-// op(A)[16 w + lane % 16][4 s + lane / 16] (complex), op(A) = A or A^H.
-template <typename R, int NB>
-struct Frag {
-  cx<R> a[NB / 4];
-};
-
-// k ranges [k0, k1) are multiples of 16 and the same for the whole wave
-// (readfirstlane makes that visible to the compiler, so that the range test
-// is one scalar branch per 16-row chunk and a chunk's LDS reads issue
-// together).  TS: A points at the transposed copy of the block (CONJT only),
-// so that the 16 lanes of a fragment row read consecutive elements.
-template <typename R, int NB, bool CONJT, typename PA, bool TS = false>
-__device__ __forceinline__ void frag_load(Frag<R, NB>& f, PA A, int w, int lane, int k0, int k1) {
-  const int i = 16 * w + (lane & 15), kq = lane >> 4;
-  const int c0 = __builtin_amdgcn_readfirstlane(k0) >> 4;
-  const int c1 = __builtin_amdgcn_readfirstlane(k1) >> 4;
-#pragma unroll
-  for (int ch = 0; ch < NB / 16; ++ch) {
-    if (ch < c0 || ch >= c1) continue;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = 16 * ch + 4 * q + kq;
-      f.a[4 * ch + q] = (CONJT && !TS) ? A[(size_t)i * NB + k] : A[(size_t)k * NB + i];
-    }
-  }
-}
-
-// acc += op(A) * B over k in [k0, k1) from prefetched fragments; NEG
-// subtracts.  B row k is LDS row rmap[k] (or k when rmap is null), row
-// stride ldb elements, columns from cb0.
-template <typename R, int NB, int NC, bool CONJT, bool NEG>
-__device__ __forceinline__ void frag_mma(Acc<R, NC>& acc, const Frag<R, NB>& f, const cx<R>* Bl,
-                                         int ldb, const int* rmap, int cb0, int lane, int k0,
-                                         int k1) {
-  const int kq = lane >> 4;
-  const int j = lane & 15;
-  const int c0 = __builtin_amdgcn_readfirstlane(k0) >> 4;
-  const int c1 = __builtin_amdgcn_readfirstlane(k1) >> 4;
-#pragma unroll
-  for (int ch = 0; ch < NB / 16; ++ch) {
-    if (ch < c0 || ch >= c1) continue;
-    cx<R> bv[4][NC];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = 16 * ch + 4 * q + kq;
-      const int br = rmap ? rmap[k] : k;
-      const cx<R>* bp = Bl + (size_t)br * ldb + cb0 + j;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) bv[q][c] = bp[16 * c];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      cx<R> a = f.a[4 * ch + q];
-      R ar = a.x, ai = CONJT ? -a.y : a.y;
-      if (NEG) {
-        ar = -ar;
-        ai = -ai;
-      }
-      const R as = ar + ai;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        acc.p1[c] = MF<R>::mma(ar, bv[q][c].x, acc.p1[c]);
-        acc.p2[c] = MF<R>::mma(ai, bv[q][c].y, acc.p2[c]);
-        acc.p3[c] = MF<R>::mma(as, bv[q][c].x + bv[q][c].y, acc.p3[c]);
-      }
-    }
-  }
-}
-
-template <typename R, int NB, int NC, bool CONJT, bool NEG, typename PA>
-__device__ __forceinline__ void wave_prod(Acc<R, NC>& acc, PA A, const cx<R>* Bl, int ldb,
-                                          const int* rmap, int w, int cb0, int lane, int k0,
-                                          int k1) {
-  Frag<R, NB> f;
-  frag_load<R, NB, CONJT>(f, A, w, lane, k0, k1);
-  frag_mma<R, NB, NC, CONJT, NEG>(acc, f, Bl, ldb, rmap, cb0, lane, k0, k1);
-}
-
-// accumulator <-> LDS rows (rows 16 w + MF<R>::row(lane, r), columns 16 c + lane%16)
-template <typename R, int NC>
-__device__ __forceinline__ void acc_to_lds(const Acc<R, NC>& acc, cx<R>* L, int ldb,
-                                           const int* rmap, int w, int cb0, int lane) {
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      int row = 16 * w + MF<R>::row(lane, r);
-      int lr = rmap ? rmap[row] : row;
-      L[(size_t)lr * ldb + cb0 + 16 * c + (lane & 15)] = acc.get(c, r);
-    }
-}
-template <typename R, int NC>
-__device__ __forceinline__ void acc_from_lds(Acc<R, NC>& acc, const cx<R>* L, int ldb,
-                                             const int* rmap, int w, int cb0, int lane) {
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      int row = 16 * w + MF<R>::row(lane, r);
-      int lr = rmap ? rmap[row] : row;
-      acc.set(c, r, L[(size_t)lr * ldb + cb0 + 16 * c + (lane & 15)]);
-    }
-}
 
 static __device__ __forceinline__ int remap_job(int bid, int njobs) {
   // consecutive jobs (one system's tiles) on one XCD: workgroups are dealt
@@ -175,628 +16,476 @@ static __device__ __forceinline__ int remap_job(int bid, int njobs) {
   return (bid % 8) * per + bid / 8;
 }
 
-// One block's initial accumulator values for a wave, raw (c128 for the
-// right-hand sides, the factors' type for the intermediates), converted when
-// first used so that the loads do not wait where they are issued.
-template <typename E, int NC>
-struct PreT {
-  E v[NC][4];
-  int k;
-};
 
-// ---------------------------------------------------------------- chunk streaming
-// The streamed form of a step's two block products: chunk ch is columns
-// 16 ch .. 16 ch + 15 of op(A) for the wave's 16 rows (four complex values
-// per lane), loaded RD chunks ahead of the MFMAs that use it, across the two
-// products and into the next step (the carry), so that only RD + 1 chunks
-// live in registers instead of whole fragments.  TR: element (i, k) of op(A)
-// at A[i NB + k] (a conjugate transpose read from the block itself), else at
-// A[k NB + i].
+// Chunk of op(A): columns 16 ch .. 16 ch + 15 for the wave's 16 rows, element
+// (16 w + lane % 16, 16 ch + 4 q + lane / 16) in a[q].
 template <typename R>
 struct Ck {
   cx<R> a[4];
 };
 
-template <typename R, int NB, bool TR>
-__device__ __forceinline__ void ck_load(Ck<R>& c, const cx<R>* A, int w, int lane, int ch) {
-  const int i = 16 * w + (lane & 15), kq = lane >> 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = 16 * ch + 4 * q + kq;
-    c.a[q] = TR ? A[(size_t)i * NB + k] : A[(size_t)k * NB + i];
-  }
-}
-
-template <typename R, bool CONJT, bool NEG>
-__device__ __forceinline__ void ck_mma(Acc<R, 1>& acc, const Ck<R>& c, const cx<R>* Bl, int ldb,
-                                       const int* rmap, int cb0, int lane, int ch) {
-  const int kq = lane >> 4, j = lane & 15;
-  cx<R> bv[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = 16 * ch + 4 * q + kq;
-    const int br = rmap ? rmap[k] : k;
-    bv[q] = Bl[(size_t)br * ldb + cb0 + j];
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    R ar = c.a[q].x, ai = CONJT ? -c.a[q].y : c.a[q].y;
-    if (NEG) {
-      ar = -ar;
-      ai = -ai;
-    }
-    acc.p1[0] = MF<R>::mma(ar, bv[q].x, acc.p1[0]);
-    acc.p2[0] = MF<R>::mma(ai, bv[q].y, acc.p2[0]);
-    acc.p3[0] = MF<R>::mma(ar + ai, bv[q].x + bv[q].y, acc.p3[0]);
-  }
-}
-
-// acc += op(A0) B0 (NEG0: -=), mid(), acc += op(A1) B1 (NEG1: -=), both over
-// all NB columns; carry holds the first RD chunks of A0 on entry and, when
-// more, of Anext (the next step's A0) on exit (RD <= NB / 16).
-template <typename R, int NB, bool TR, bool CONJT, bool NEG0, bool NEG1, int RD, class Mid>
-__device__ __forceinline__ void stream_step(Acc<R, 1>& acc, Ck<R> (&carry)[RD], const cx<R>* A0,
-                                            const cx<R>* A1, const cx<R>* Anext, bool more,
-                                            const cx<R>* B0, const cx<R>* B1, const int* rm0,
-                                            const int* rm1, int ldb, int cb0, int w, int lane,
-                                            Mid mid) {
-  constexpr int NCH = NB / 16, L = 2 * NCH;
-  static_assert(RD >= 1 && RD <= NCH, "the carry holds chunks of the first product only");
-  Ck<R> buf[L + RD];
-#pragma unroll
-  for (int i = 0; i < RD; ++i) buf[i] = carry[i];
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int ip = i + RD;
-    if (ip < L)
-      ck_load<R, NB, TR>(buf[ip], ip < NCH ? A0 : A1, w, lane, ip % NCH);
-    else if (more)
-      ck_load<R, NB, TR>(buf[ip], Anext, w, lane, ip - L);
-    if (i == NCH) mid();
-    if (i < NCH)
-      ck_mma<R, CONJT, NEG0>(acc, buf[i], B0, ldb, rm0, cb0, lane, i);
-    else
-      ck_mma<R, CONJT, NEG1>(acc, buf[i], B1, ldb, rm1, cb0, lane, i - NCH);
-  }
-#pragma unroll
-  for (int i = 0; i < RD; ++i) carry[i] = buf[L + i];
-}
-
 // ---------------------------------------------------------------- MFMA block solve
-// One workgroup per job with one wave per 16 x (16 NC) output tile of a block
-// product ((NB/16) x (T/(16 NC)) waves; a wave with NC > 1 reuses each factor
-// fragment for NC column tiles).  LDS holds 3 slots of NB x T (rows padded to
-// T + 1 elements) and the block's permutation with its inverse.  Every tile
-// that enters or leaves global memory goes through an LDS slot with thread
-// e on row e % NB, column e / NB, so that a wave reads or writes whole column
-// runs of 64 rows.  OCC > 1 asks the compiler to fit the registers of OCC
-// waves per SIMD.
-template <typename R, int NB, int T, bool PREF, int NC, int OCC, bool STR = false>
-__global__ void __launch_bounds__(NB * 4 * (T / (16 * NC)), OCC)
+// NB / 16 waves per job, wave w computing rows 16 w .. 16 w + 15 of every
+// product for the tile's 16 NC columns.  Tiles are computed transposed (the
+// right-hand sides are the first MFMA operand), so that a lane's
+// accumulators belong to one block row, lane % 16, and four columns: 16 lanes
+// cover 16 consecutive rows of a column, and right-hand sides, intermediates
+// and solutions move between global memory and the accumulators in runs of
+// 128 or 256 bytes, without a detour through LDS.  LDS holds three slots of
+// NB x 16 NC (panels of 16 columns; within a row the columns are permuted by
+// the row, which keeps the accumulators' writes off each other's banks) and
+// the block's permutation.  Factor fragments stream from L2 RD chunks ahead
+// of the MFMAs that use them, across products, barriers and steps.
+//
+// What bounds it: the MFMAs (4 NB complex multiply-adds per element of x) and,
+// not fully overlapped, the right-hand sides, intermediates and solutions in
+// HBM (48 bytes per element of x, 64 for a correction).  Sweeps are chains of
+// steps, so that several workgroups have to share a CU: three slots instead of
+// staging buffers for every transfer, loads and stores without branches in
+// full tiles, and registers for two waves per SIMD or more.  At n = 16384,
+// complex64, b = 64, 64 system-directions of 1400 columns: 23.4 ms (MFMA
+// alone 15, HBM alone 14.6) against 40.4 in a form that staged every tile
+// through LDS; b = 128, 64 of 576: 19.5 against 34.8 (12.3); complex128, b =
+// 64, 48 of 1056: 27.7 against 37.6 (17.6).
+template <typename R, int NB, int NC>
+__global__ void __launch_bounds__(NB * 4, 2)
 k_band_solve(const cx<R>* __restrict__ mats, const cx<R>* __restrict__ matsT,
              const int16_t* __restrict__ permg, int64_t n, int K,
              const SolveJob* __restrict__ jobs, int njobs, const int32_t* __restrict__ gate) {
-  // complex64 H solves read the transposed copy of the factor blocks
-  constexpr bool TS = sizeof(R) == 4;
-  constexpr int LDT = T + 1;    // LDS row of a slot
-  constexpr int SL = NB * LDT;  // one slot
+  constexpr bool TS = sizeof(R) == 4;  // H solves read the transposed copy
+  constexpr int NCH = NB / 16;
+  constexpr int L = 2 * NCH;
+  constexpr int RD = NCH < 2 ? NCH : 2;  // chunks in flight
+  constexpr int T = 16 * NC;
+  constexpr int SL = NB * T;                   // elements of a slot
+  constexpr int RB = 16 * (int)sizeof(cx<R>);  // bytes of a panel row
+  using E = cx<R>;
+  using Acc1 = Acc<R, NC>;
   extern __shared__ __align__(16) char lds_raw[];
-  int* sp = reinterpret_cast<int*>(lds_raw);  // permutation, 2 NB entries
-  int* si = sp + 2 * NB;                      // its inverse
-  cx<R>* S = reinterpret_cast<cx<R>*>(lds_raw + ((4 * NB * sizeof(int) + 15) & ~15));
+  E* S = reinterpret_cast<E*>(lds_raw);
+  uint16_t* spt = reinterpret_cast<uint16_t*>(lds_raw + 3 * SL * sizeof(E));  // gather offsets
+  uint16_t* spo = spt + NB;                                                    // window row offsets
   const int job = remap_job(blockIdx.x, njobs);
   if (job >= njobs) return;
   const SolveJob jb = jobs[job];
   if (gate && !gate[jb.grp]) return;  // a correction its group no longer needs
   const int t = threadIdx.x, lane = t & 63;
-  constexpr int NRW = NB / 16;
-  // row block and column base of this wave (wave-uniform: scalar registers)
-  const int w = __builtin_amdgcn_readfirstlane((t >> 6) % NRW);
-  const int cb0 = __builtin_amdgcn_readfirstlane(16 * NC * ((t >> 6) / NRW));
-  constexpr int NTHR = NB * 4 * (T / (16 * NC));
-  constexpr int RF = NB * T / NTHR;  // tile elements per thread
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int li = lane & 15, kq = lane >> 4;
+  const int row = 16 * w + li;  // the lane's block row
   const size_t bb = (size_t)NB * NB;
-  const cx<R>* F = mats + (size_t)jb.sys * K * 5 * bb;
+  const E* F = mats + (size_t)jb.sys * K * 5 * bb;
+  const E* FT = TS ? matsT + (size_t)jb.sys * K * 5 * bb : F;
   const int16_t* P = permg + (size_t)jb.sys * K * 2 * NB;
-  const c128* in = jb.in + (int64_t)jb.col0 * jb.ldin;
-  cx<R>* mid = reinterpret_cast<cx<R>*>(jb.mid) + (int64_t)jb.col0 * jb.ldmid;
-  c128* out = jb.out + (int64_t)jb.col0 * jb.ldout;
   const int ncol = jb.ncol;
-
-  // Global loads are branch-free (an out-of-range element reads the tile's
-  // first element and is zeroed when used), so that a group of loads issues
-  // together and waits once, where its values are first needed.
-  auto okf = [&](int64_t row, int col) { return row < n && col < ncol; };
-  auto gaddr = [&](auto base, int64_t ld, int64_t row, int col) {
-    return base + (okf(row, col) ? (int64_t)col * ld + row : 0);
-  };
-  auto conv = [&](auto v, bool ok) -> cx<R> {
-    return ok ? mk<R>((R)v.x, (R)v.y) : mk<R>(0, 0);
-  };
-  // tile element q of this thread: row e % NB, column e / NB
-  auto erow = [&](int q) { return (t + q * NTHR) % NB; };
-  auto ecol = [&](int q) { return (t + q * NTHR) / NB; };
-  struct TileC {
-    c128 v[RF];
-  };
-  struct TileR {
-    cx<R> v[RF];
-  };
-  // global rows row0 .. row0 + NB - 1 of a tile into registers, then LDS
-  auto tile_issue = [&](auto& f, auto base, int64_t ld, int64_t row0) {
-#pragma unroll
-    for (int q = 0; q < RF; ++q) f.v[q] = gld(gaddr(base, ld, row0 + erow(q), ecol(q)));
-  };
-  auto tile_store = [&](const auto& f, cx<R>* dst, int64_t row0) {
-#pragma unroll
-    for (int q = 0; q < RF; ++q)
-      dst[erow(q) * LDT + ecol(q)] = conv(f.v[q], okf(row0 + erow(q), ecol(q)));
-  };
-  // values v[q] of rows row0 + erow(q) into the output (added to it for a
-  // correction): all loads of the old values first, then the stores
-  auto emit_vals = [&](const cx<R>* v, int64_t row0) {
-    c128 old[RF];
-    if (jb.add) {
-#pragma unroll
-      for (int q = 0; q < RF; ++q) old[q] = gld(gaddr(out, jb.ldout, row0 + erow(q), ecol(q)));
-    }
-#pragma unroll
-    for (int q = 0; q < RF; ++q) {
-      const int64_t row = row0 + erow(q);
-      if (!okf(row, ecol(q))) continue;
-      c128 x = mk((double)v[q].x, (double)v[q].y);
-      if (jb.add) x = old[q] + x;
-      gst(out + (int64_t)ecol(q) * jb.ldout + row, x);
-    }
-  };
-  auto emit_tile = [&](const cx<R>* src, int64_t row0) {
-    cx<R> v[RF];
-#pragma unroll
-    for (int q = 0; q < RF; ++q) v[q] = src[erow(q) * LDT + ecol(q)];
-    emit_vals(v, row0);
-  };
-  auto put_mid = [&](const cx<R>* src, int64_t row0) {
-#pragma unroll
-    for (int q = 0; q < RF; ++q) {
-      const int64_t row = row0 + erow(q);
-      if (okf(row, ecol(q)))
-        gst(mid + (int64_t)ecol(q) * jb.ldmid + row, src[erow(q) * LDT + ecol(q)]);
-    }
-  };
-  auto zero_slots = [&](cx<R>* dst, int nslot) {
-    for (int e = t; e < nslot * SL; e += NTHR) dst[e] = mk<R>(0, 0);
-  };
-  // the permutation of block k and its inverse
-  auto perm_put = [&](int e, int v) {
-    sp[e] = v;
-    if ((unsigned)v < (unsigned)(2 * NB)) si[v] = e;
-  };
-  auto load_perm = [&](int k) {
-    for (int e = t; e < 2 * NB; e += NTHR) perm_put(e, gld(P + (size_t)k * 2 * NB + e));
-  };
-  // fetched early into registers, stored later
-  constexpr int RP = (2 * NB + NTHR - 1) / NTHR;
-  struct PermPre {
-    int16_t v[RP];
-  };
-  auto perm_issue = [&](PermPre& pp, int k) {
-#pragma unroll
-    for (int q = 0; q < RP; ++q) {
-      const int e = t + q * NTHR;
-      pp.v[q] = gld(P + (size_t)k * 2 * NB + (e < 2 * NB ? e : 0));
-    }
-  };
-  auto perm_store = [&](const PermPre& pp) {
-#pragma unroll
-    for (int q = 0; q < RP; ++q) {
-      const int e = t + q * NTHR;
-      if (e < 2 * NB) perm_put(e, pp.v[q]);
-    }
-  };
   auto blk = [&](int k, int slot) { return F + ((size_t)k * 5 + slot) * bb; };
-  const cx<R>* FT = TS ? matsT + (size_t)jb.sys * K * 5 * bb : F;
   auto blkh = [&](int k, int slot) { return FT + ((size_t)k * 5 + slot) * bb; };
-  // initial accumulator values for the wave's rows of block k, prefetched
-  // into registers one step ahead
-  auto pre_load = [&](auto& p, auto base, int64_t ld, int k) {
-    p.k = k;
+
+  // ---- global tiles in accumulator order.  Columns beyond ncol read the
+  // first one (never stored); rows beyond n are zeroed by the user.
+  const int colg = MF<R>::row(lane, 0), colr = MF<R>::row(0, 1);
+  auto col_of = [&](int c, int r) { return 16 * c + colg + colr * r; };
+  auto gtile = [&](auto (&v)[NC][4], auto base, int64_t ld, int k) {
+    const int64_t i = (int64_t)k * NB + row;
+    const auto p0 = base + (i < n ? i : n - 1);
+    const auto pl = p0 + colg * ld;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        p.v[c][r] = gld(gaddr(base, ld, (int64_t)k * NB + 16 * w + MF<R>::row(lane, r),
-                              cb0 + 16 * c + (lane & 15)));
+        v[c][r] = gld(col_of(c, r) < ncol ? pl + (16 * c + colr * r) * ld : p0);
   };
-  auto pre_to_acc = [&](Acc<R, NC>& acc, const auto& p) {
+  auto rowok = [&](int k) { return (int64_t)k * NB + row < n; };
+  auto gput = [&](const auto (&v)[NC][4], auto base, int64_t ld, int k) {
+    auto pl = base + ((int64_t)k * NB + row) + colg * ld;
+    if (ncol == T && (int64_t)(k + 1) * NB <= n) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) gst(pl + (16 * c + colr * r) * ld, v[c][r]);
+    } else if (rowok(k)) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (col_of(c, r) < ncol) gst(pl + (16 * c + colr * r) * ld, v[c][r]);
+    }
+  };
+  const c128* in = jb.in + (int64_t)jb.col0 * jb.ldin;
+  E* mid = reinterpret_cast<E*>(jb.mid) + (int64_t)jb.col0 * jb.ldmid;
+  c128* out = jb.out + (int64_t)jb.col0 * jb.ldout;
+
+  // ---- LDS tiles.  Element (row i, column c) of a slot: panel c / 16, row
+  // i, place (c % 16) ^ 4 (i % 4).
+  auto lput = [&](E* panel, int sw, const E (&v)[4]) {
+    if constexpr (sizeof(R) == 4) {
+      float4* p = reinterpret_cast<float4*>(panel + ((4 * kq) ^ (sw << 2)));
+      p[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+      p[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) panel[kq + 4 * (r ^ sw)] = v[r];
+    }
+  };
+  auto lget = [&](const E* panel, int sw, E (&v)[4]) {
+    if constexpr (sizeof(R) == 4) {
+      const float4* p = reinterpret_cast<const float4*>(panel + ((4 * kq) ^ (sw << 2)));
+      const float4 a = p[0], b = p[1];
+      v[0] = mk<R>(a.x, a.y);
+      v[1] = mk<R>(a.z, a.w);
+      v[2] = mk<R>(b.x, b.y);
+      v[3] = mk<R>(b.z, b.w);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const E* p = panel + kq + 4 * (r ^ sw);
+        v[r] = mk<R>(p->x, p->y);
+      }
+    }
+  };
+  auto put_own = [&](int slot, const E (&v)[NC][4]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) lput(S + slot * SL + (c * NB + row) * 16, li & 3, v[c]);
+  };
+  auto get_own = [&](int slot, E (&v)[NC][4]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) lget(S + slot * SL + (c * NB + row) * 16, li & 3, v[c]);
+  };
+  // window row d of slots 0 (rows 0 .. NB - 1) and 1 (NB .. 2 NB - 1): byte
+  // offset of its row in panel 0, and 4 (d % 4) elements in the low bits
+  auto woff = [&](int d) {
+    return (d < NB ? d : d + NB * (NC - 1)) * RB + (d & 3) * 4 * (int)sizeof(E);
+  };
+  auto win = [&](int off, int c) {
+    return reinterpret_cast<E*>(lds_raw + (off & ~(RB - 1)) + c * NB * RB);
+  };
+  auto win_sw = [&](int off) { return (off & (RB - 1)) / (4 * (int)sizeof(E)); };
+  // row d of a tile in registers, in the factors' type
+  auto conv = [&](const auto (&v)[NC][4], bool ok, E (&x)[NC][4]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[c][r] = mk<R>(ok ? (R)v[c][r].x : (R)0, ok ? (R)v[c][r].y : (R)0);
+  };
+  auto acc_set = [&](Acc1& acc, const E (&v)[NC][4]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc.set(c, r, v[c][r]);
+  };
+  auto acc_get = [&](const Acc1& acc, E (&v)[NC][4]) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[c][r] = acc.get(c, r);
+  };
+  // the solution's rows of block k (added to the old values for a correction)
+  auto emit = [&](const E (&x)[NC][4], const c128 (&old)[NC][4], int k) {
+    c128 o[NC][4];
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        acc.set(c, r, conv(p.v[c][r], okf((int64_t)p.k * NB + 16 * w + MF<R>::row(lane, r),
-                                          cb0 + 16 * c + (lane & 15))));
+        o[c][r] = mk((double)x[c][r].x, (double)x[c][r].y);
+        if (jb.add) o[c][r] = old[c][r] + o[c][r];
       }
+    gput(o, out, jb.ldout, k);
   };
-  Acc<R, NC> acc;
-  Frag<R, NB> fa, fb, fc;
-  PreT<cx<R>, NC> pvm;  // intermediates (N backward)
-  PreT<c128, NC> pvi;   // right-hand sides (H forward)
+  // permutation of block k: one entry per thread (again from the first
+  // beyond 2 NB)
+  const int pe = t % (2 * NB);
+  auto perm_get = [&](int k) { return gld(P + (size_t)k * 2 * NB + pe); };
+  auto perm_put = [&](int v) {
+    const uint16_t o = (uint16_t)woff(v);
+    spo[pe] = o;
+    // gather order of the top rows: entry 16 ch + 4 q + kq at [ch][kq][q]
+    if (pe < NB) spt[(pe & ~15) + 4 * (pe & 3) + ((pe >> 2) & 3)] = o;
+  };
 
-  if constexpr (STR) {
-    static_assert(NC == 1, "streamed products take one 16-column tile per wave");
-    // chunks in flight: the carry into the next step holds chunks of its
-    // first product only, so at most that product's NB / 16 chunks
-    constexpr int RD = NB >= 32 ? 2 : 1;
-    Ck<R> carry[RD];
-    auto none = [] {};
-    if (jb.dir == 0) {
-      // ------------------------------------------------------- N forward
-      cx<R>* W = S;
-      cx<R>* Yt = S + 2 * SL;
-      {
-        TileC f0, f1;
-        tile_issue(f0, in, jb.ldin, 0);
-        tile_issue(f1, in, jb.ldin, NB);
-        tile_store(f0, W, 0);
-        tile_store(f1, W + SL, NB);
-      }
-      TileC fr;
-      load_perm(0);
+  // ---- products
+  auto ck_load = [&](Ck<R>& c, const E* A, bool tr, int ch) {
 #pragma unroll
-      for (int i = 0; i < RD; ++i) ck_load<R, NB, false>(carry[i], blk(0, 0), w, lane, i);
-      __syncthreads();
-      for (int k = 0; k < K; ++k) {
-        PermPre pnext;
-        acc.zero();
-        const bool more = k + 1 < K;
-        stream_step<R, NB, false, false, false, true, RD>(
-            acc, carry, blk(k, 0), blk(k, 1), blk(more ? k + 1 : k, 0), more, W, W, sp, sp, LDT,
-            cb0, w, lane, [&] {
-              acc_to_lds(acc, Yt, LDT, nullptr, w, cb0, lane);
-              tile_issue(fr, in, jb.ldin, (int64_t)(k + 2) * NB);
-              if (k + 1 < K) perm_issue(pnext, k + 1);
-              acc_from_lds(acc, W, LDT, sp + NB, w, cb0, lane);
-            });
-        __syncthreads();
-        acc_to_lds(acc, W, LDT, nullptr, w, cb0, lane);
-        tile_store(fr, W + SL, (int64_t)(k + 2) * NB);
-        put_mid(Yt, (int64_t)k * NB);
-        if (k + 1 < K) perm_store(pnext);
-        __syncthreads();
-      }
-      // ------------------------------------------------------- N backward
-      // blocks beyond the last (G1(K-1), G2(K-2), G2(K-1)) are zero, as are
-      // the x slots beyond x_{K-1}: every step runs both products
-      cx<R>* X1 = S;
-      cx<R>* X2 = S + SL;
-      cx<R>* V = S + 2 * SL;
-      zero_slots(S, 2);
-      pre_load(pvm, mid, jb.ldmid, K - 1);
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * ch + 4 * q;
+      c.a[q] = tr ? gld(A + k + (row * NB + kq)) : gld(A + k * NB + (kq * NB + row));
+    }
+  };
+  // rows 16 ch + 4 q + kq of a slot, column li of every panel
+  auto b_slot = [&](int slot) {
+    return [=](int ch, E (&bv)[4][NC]) {
+      const E* p = S + slot * SL + kq * 16 + (li ^ (kq << 2));
 #pragma unroll
-      for (int i = 0; i < RD; ++i) ck_load<R, NB, false>(carry[i], blk(K - 1, 3), w, lane, i);
-      __syncthreads();
-      for (int k = K - 1; k >= 0; --k) {
-        pre_to_acc(acc, pvm);
-        const bool more = k > 0;
-        stream_step<R, NB, false, false, true, true, RD>(
-            acc, carry, blk(k, 3), blk(k, 4), blk(more ? k - 1 : k, 3), more, X1, X2, nullptr,
-            nullptr, LDT, cb0, w, lane, none);
-        acc_to_lds(acc, V, LDT, nullptr, w, cb0, lane);
-        if (k > 0) pre_load(pvm, mid, jb.ldmid, k - 1);
-        if (k + 1 < K) emit_tile(X1, (int64_t)(k + 1) * NB);
-        __syncthreads();
-        cx<R>* tmp = X2;
-        X2 = X1;
-        X1 = V;
-        V = tmp;
-      }
-      emit_tile(X1, 0);
-    } else {
-      // ------------------------------------------------------- H forward
-      // G1(k-1)^H and G2(k-2)^H meet zero slots before the first steps
-      // (block 0 stands in for the missing ones)
-      constexpr bool TRH = !TS;
-      cx<R>* W1 = S;
-      cx<R>* W2 = S + SL;
-      cx<R>* V = S + 2 * SL;
-      zero_slots(S, 2);
-      pre_load(pvi, in, jb.ldin, 0);
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int i = 0; i < RD; ++i) ck_load<R, NB, TRH>(carry[i], blkh(0, 3), w, lane, i);
-      __syncthreads();
-      for (int k = 0; k < K; ++k) {
-        pre_to_acc(acc, pvi);
-        const bool more = k + 1 < K;
-        stream_step<R, NB, TRH, true, true, true, RD>(
-            acc, carry, blkh(k >= 1 ? k - 1 : 0, 3), blkh(k >= 2 ? k - 2 : 0, 4), blkh(k, 3), more,
-            W1, W2, nullptr, nullptr, LDT, cb0, w, lane, none);
-        acc_to_lds(acc, V, LDT, nullptr, w, cb0, lane);
-        if (k >= 1) put_mid(W1, (int64_t)(k - 1) * NB);
-        if (k + 1 < K) pre_load(pvi, in, jb.ldin, k + 1);
-        __syncthreads();
-        cx<R>* tmp = W2;
-        W2 = W1;
-        W1 = V;
-        V = tmp;
-      }
-      put_mid(W1, (int64_t)(K - 1) * NB);
-      __syncthreads();
-      // ------------------------------------------------------- H backward
-      cx<R>* Cb = S;
-      cx<R>* Wk = S + SL;
-      cx<R>* Vt = S + 2 * SL;
-      zero_slots(Cb, 1);
-      {
-        TileR f0;
-        tile_issue(f0, mid, jb.ldmid, (int64_t)(K - 1) * NB);
-        tile_store(f0, Wk, (int64_t)(K - 1) * NB);
-      }
-      load_perm(K - 1);
+        for (int c = 0; c < NC; ++c) bv[q][c] = p[(c * NB + 16 * ch + 4 * q) * 16];
+    };
+  };
+  Ck<R> carry[RD];
+  auto mma = [&](Acc1& acc, const Ck<R>& ck, const E (&bv)[4][NC], bool conj, bool neg) {
 #pragma unroll
-      for (int i = 0; i < RD; ++i) ck_load<R, NB, TRH>(carry[i], blkh(K - 1, 0), w, lane, i);
-      __syncthreads();
-      for (int k = K - 1; k >= 0; --k) {
-        acc.zero();
-        const bool more = k > 0;
-        stream_step<R, NB, TRH, true, false, true, RD>(
-            acc, carry, blkh(k, 0), blkh(k, 1), blkh(more ? k - 1 : k, 0), more, Wk, Cb, nullptr,
-            nullptr, LDT, cb0, w, lane, none);
-        TileR fw;
-        PermPre pnext;
-        if (k > 0) {
-          tile_issue(fw, mid, jb.ldmid, (int64_t)(k - 1) * NB);
-          perm_issue(pnext, k - 1);
+    for (int q = 0; q < 4; ++q) {
+      R ar = ck.a[q].x, ai = conj ? -ck.a[q].y : ck.a[q].y;
+      if (neg) {
+        ar = -ar;
+        ai = -ai;
+      }
+      const R as = ar + ai;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        acc.p1[c] = MF<R>::mma(bv[q][c].x, ar, acc.p1[c]);
+        acc.p2[c] = MF<R>::mma(bv[q][c].y, ai, acc.p2[c]);
+        acc.p3[c] = MF<R>::mma(bv[q][c].x + bv[q][c].y, as, acc.p3[c]);
+      }
+    }
+  };
+  // acc += op(A0) B0, mid(), acc -= op(A1) B1 (neg0: acc -= op(A0) B0); carry
+  // holds the first chunks of A0 on entry and of An (the next step's A0) on exit
+  auto step = [&](Acc1& acc, const E* A0, const E* A1, const E* An, auto B0, auto B1, bool conj,
+                  bool neg0, auto midf) {
+    const bool tr = conj && !TS;
+    Ck<R> buf[L + RD];
+#pragma unroll
+    for (int i = 0; i < RD; ++i) buf[i] = carry[i];
+    E bv[2][4][NC];
+    B0(0, bv[0]);
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int ip = i + RD;
+      ck_load(buf[ip], ip < NCH ? A0 : (ip < L ? A1 : An), tr, ip % NCH);
+      if (i + 1 < L) {
+        if (i + 1 < NCH)
+          B0(i + 1, bv[(i + 1) & 1]);
+        else
+          B1(i + 1 - NCH, bv[(i + 1) & 1]);
+      }
+      if (i == NCH) midf();
+      mma(acc, buf[i], bv[i & 1], conj, i < NCH ? neg0 : true);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < RD; ++i) carry[i] = buf[L + i];
+  };
+  auto start = [&](const E* A, bool conj) {
+#pragma unroll
+    for (int i = 0; i < RD; ++i) ck_load(carry[i], A, conj && !TS, i);
+  };
+  auto none = [] {};
+
+  Acc1 acc;
+  E x[NC][4];
+  c128 old[NC][4];
+  E zero[NC][4];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) zero[c][r] = mk<R>(0, 0);
+  if (jb.dir == 0) {
+    // ---------------------------------------------------------- N forward
+    // window = slots 0 (carry) and 1 (the block's new rows): v_k = Q z_top and
+    // the next carry z_bot - M z_top, z = P y_win
+    c128 fr[NC][4];
+    gtile(fr, in, jb.ldin, 0);
+    int pv = perm_get(0);
+    start(blk(0, 0), false);
+    conv(fr, rowok(0), x);
+    put_own(0, x);
+    gtile(fr, in, jb.ldin, 1);
+    perm_put(pv);
+    conv(fr, rowok(1), x);
+    put_own(1, x);
+    gtile(fr, in, jb.ldin, 2);
+    pv = perm_get(K > 1 ? 1 : 0);
+    __syncthreads();
+    for (int k = 0; k < K; ++k) {
+      uint2 off[NCH];  // gather offsets of the rows 16 ch + 4 q + kq
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch)
+        off[ch] = *reinterpret_cast<const uint2*>(spt + 16 * ch + 4 * kq);
+      auto b_win = [&](int ch, E (&bv)[4][NC]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const unsigned h = q < 2 ? off[ch].x : off[ch].y;
+          const unsigned o = ((q & 1) ? h >> 16 : h & 0xffffu) ^ (li * (unsigned)sizeof(E));
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            bv[q][c] = *reinterpret_cast<const E*>(lds_raw + o + c * NB * RB);
         }
-        acc_to_lds(acc, Vt, LDT, nullptr, w, cb0, lane);
-        __syncthreads();
-        {
-          cx<R> cv[RF], lv[RF];
+      };
+      const int zo = spo[NB + row];
+      acc.zero();
+      step(acc, blk(k, 0), blk(k, 1), blk(k + 1 < K ? k + 1 : k, 0), b_win, b_win, false, false,
+           [&] {
+             acc_get(acc, x);
+             E z[NC][4];
 #pragma unroll
-          for (int q = 0; q < RF; ++q) {
-            const int r = erow(q), col = ecol(q);
-            const int ic = si[r], il = si[NB + r];
-            cv[q] = ic < NB ? Vt[ic * LDT + col] : Cb[(ic - NB) * LDT + col];
-            lv[q] = il < NB ? Vt[il * LDT + col] : Cb[(il - NB) * LDT + col];
-          }
-#pragma unroll
-          for (int q = 0; q < RF; ++q) Wk[erow(q) * LDT + ecol(q)] = cv[q];
-          emit_vals(lv, (int64_t)k * NB + NB);
-        }
-        __syncthreads();
-        if (k > 0) {
-          tile_store(fw, Cb, (int64_t)(k - 1) * NB);
-          perm_store(pnext);
-        }
-        cx<R>* tmp = Cb;
-        Cb = Wk;
-        Wk = tmp;
-        __syncthreads();
-      }
-      emit_tile(Cb, 0);
+             for (int c = 0; c < NC; ++c) lget(win(zo, c), win_sw(zo), z[c]);
+             acc_set(acc, z);
+             gput(x, mid, jb.ldmid, k);
+           });
+      __syncthreads();
+      acc_get(acc, x);
+      put_own(0, x);
+      conv(fr, rowok(k + 2), x);
+      put_own(1, x);
+      perm_put(pv);
+      gtile(fr, in, jb.ldin, k + 3 <= K ? k + 3 : K);
+      pv = perm_get(k + 2 < K ? k + 2 : K - 1);
+      __syncthreads();
+    }
+    // ---------------------------------------------------------- N backward
+    // x_k = v_k - G1 x_{k+1} - G2 x_{k+2}; the blocks beyond the last are
+    // zero, as are the slots of x_K and x_{K+1}
+    int s1 = 0, s2 = 1, sv = 2;
+    put_own(0, zero);
+    put_own(1, zero);
+    E pm[NC][4];
+    gtile(pm, mid, jb.ldmid, K - 1);
+    start(blk(K - 1, 3), false);
+    conv(pm, rowok(K - 1), x);
+    acc_set(acc, x);
+    __syncthreads();
+    for (int k = K - 1; k >= 0; --k) {
+      if (jb.add) gtile(old, out, jb.ldout, k);
+      gtile(pm, mid, jb.ldmid, k > 0 ? k - 1 : 0);
+      step(acc, blk(k, 3), blk(k, 4), blk(k > 0 ? k - 1 : k, 3), b_slot(s1), b_slot(s2), false,
+           true, none);
+      acc_get(acc, x);
+      put_own(sv, x);
+      E y[NC][4];
+      conv(pm, true, y);  // rows below n for k > 0
+      acc_set(acc, y);
+      emit(x, old, k);
+      __syncthreads();
+      const int s = s2;
+      s2 = s1;
+      s1 = sv;
+      sv = s;
     }
   } else {
-    if (jb.dir == 0) {
-      // ---------------------------------------------------------- N forward
-      // v_k = Q z_top and the next window top z_bot - M z_top are both
-      // products of z_top = rows sp[0, NB) of the window
-      cx<R>* W = S;           // window: rows 0 .. 2 NB - 1 (two slots)
-      cx<R>* Yt = S + 2 * SL; // v_k on its way to the intermediate
-      {
-        TileC f0, f1;
-        tile_issue(f0, in, jb.ldin, 0);
-        tile_issue(f1, in, jb.ldin, NB);
-        tile_store(f0, W, 0);
-        tile_store(f1, W + SL, NB);
-      }
-      TileC fr;
-      load_perm(0);
-      if (PREF) frag_load<R, NB, false>(fa, blk(0, 0), w, lane, 0, NB);
+    // ---------------------------------------------------------- H forward (U^H)
+    // u_k = y_k - G1(k-1)^H u_{k-1} - G2(k-2)^H u_{k-2}; block 0 stands in for
+    // the missing ones, which meet zero slots
+    int s1 = 0, s2 = 1, sv = 2;
+    put_own(0, zero);
+    put_own(1, zero);
+    c128 fr[NC][4];
+    gtile(fr, in, jb.ldin, 0);
+    start(blkh(0, 3), true);
+    conv(fr, rowok(0), x);
+    acc_set(acc, x);
+    __syncthreads();
+    for (int k = 0; k < K; ++k) {
+      gtile(fr, in, jb.ldin, k + 1 < K ? k + 1 : k);
+      step(acc, blkh(k >= 1 ? k - 1 : 0, 3), blkh(k >= 2 ? k - 2 : 0, 4), blkh(k, 3), b_slot(s1),
+           b_slot(s2), true, true, none);
+      acc_get(acc, x);
+      put_own(sv, x);
+      E y[NC][4];
+      conv(fr, rowok(k + 1), y);
+      acc_set(acc, y);
+      gput(x, mid, jb.ldmid, k);
       __syncthreads();
-      for (int k = 0; k < K; ++k) {
-        if (PREF) frag_load<R, NB, false>(fb, blk(k, 1), w, lane, 0, NB);
-        if (!PREF) frag_load<R, NB, false>(fa, blk(k, 0), w, lane, 0, NB);
-        acc.zero();
-        frag_mma<R, NB, NC, false, false>(acc, fa, W, LDT, sp, cb0, lane, 0, NB);
-        acc_to_lds(acc, Yt, LDT, nullptr, w, cb0, lane);
-        tile_issue(fr, in, jb.ldin, (int64_t)(k + 2) * NB);  // consumed after the product
-        PermPre pnext;
-        if (k + 1 < K) perm_issue(pnext, k + 1);
-        if (PREF && k + 1 < K) frag_load<R, NB, false>(fa, blk(k + 1, 0), w, lane, 0, NB);
-        if (!PREF) frag_load<R, NB, false>(fb, blk(k, 1), w, lane, 0, NB);
-        acc_from_lds(acc, W, LDT, sp + NB, w, cb0, lane);
-        frag_mma<R, NB, NC, false, true>(acc, fb, W, LDT, sp, cb0, lane, 0, NB);
-        __syncthreads();
-        acc_to_lds(acc, W, LDT, nullptr, w, cb0, lane);
-        tile_store(fr, W + SL, (int64_t)(k + 2) * NB);
-        put_mid(Yt, (int64_t)k * NB);
-        if (k + 1 < K) perm_store(pnext);
-        __syncthreads();
-      }
-      // ---------------------------------------------------------- N backward
-      // x_k = v_k - G1 x_{k+1} - G2 x_{k+2}, one set of products per step;
-      // x_{k+1} leaves for the output while step k runs
-      cx<R>* X1 = S;
-      cx<R>* X2 = S + SL;
-      cx<R>* V = S + 2 * SL;
-      zero_slots(S, 2);
-      // fa = G1(k), fb = G2(k), pv = v_k: prefetched (the last step uses
-      // neither block)
-      pre_load(pvm, mid, jb.ldmid, K - 1);
-      __syncthreads();
-      for (int k = K - 1; k >= 0; --k) {
-        if (!PREF && k + 1 < K) frag_load<R, NB, false>(fa, blk(k, 3), w, lane, 0, NB);
-        if (!PREF && k + 2 < K) frag_load<R, NB, false>(fb, blk(k, 4), w, lane, 0, NB);
-        pre_to_acc(acc, pvm);
-        if (k + 1 < K) frag_mma<R, NB, NC, false, true>(acc, fa, X1, LDT, nullptr, cb0, lane, 0, NB);
-        if (k + 2 < K) frag_mma<R, NB, NC, false, true>(acc, fb, X2, LDT, nullptr, cb0, lane, 0, NB);
-        acc_to_lds(acc, V, LDT, nullptr, w, cb0, lane);
-        if (k > 0) {
-          if (PREF) frag_load<R, NB, false>(fa, blk(k - 1, 3), w, lane, 0, NB);
-          if (PREF && k + 1 < K) frag_load<R, NB, false>(fb, blk(k - 1, 4), w, lane, 0, NB);
-          pre_load(pvm, mid, jb.ldmid, k - 1);
-        }
-        if (k + 1 < K) emit_tile(X1, (int64_t)(k + 1) * NB);
-        __syncthreads();
-        cx<R>* tmp = X2;
-        X2 = X1;
-        X1 = V;
-        V = tmp;
-      }
-      emit_tile(X1, 0);
-    } else {
-      // ---------------------------------------------------------- H forward (U^H)
-      // u_k = y_k - G1(k-1)^H u_{k-1} - G2(k-2)^H u_{k-2}, one set of products
-      // per step; u_{k-1} leaves for the intermediate while step k runs
-      cx<R>* W1 = S;
-      cx<R>* W2 = S + SL;
-      cx<R>* V = S + 2 * SL;
-      zero_slots(S, 2);
-      // fa = G1(k-1)^H, fb = G2(k-2)^H, pv = y_k: prefetched
-      pre_load(pvi, in, jb.ldin, 0);
-      __syncthreads();
-      for (int k = 0; k < K; ++k) {
-        if (!PREF && k >= 1) frag_load<R, NB, true, const cx<R>*, TS>(fa, blkh(k - 1, 3), w, lane, 0, NB);
-        if (!PREF && k >= 2) frag_load<R, NB, true, const cx<R>*, TS>(fb, blkh(k - 2, 4), w, lane, 0, NB);
-        pre_to_acc(acc, pvi);
-        if (k >= 1) frag_mma<R, NB, NC, true, true>(acc, fa, W1, LDT, nullptr, cb0, lane, 0, NB);
-        if (k >= 2) frag_mma<R, NB, NC, true, true>(acc, fb, W2, LDT, nullptr, cb0, lane, 0, NB);
-        acc_to_lds(acc, V, LDT, nullptr, w, cb0, lane);
-        if (k + 1 < K) {
-          if (PREF) frag_load<R, NB, true, const cx<R>*, TS>(fa, blkh(k, 3), w, lane, 0, NB);
-          if (PREF && k >= 1) frag_load<R, NB, true, const cx<R>*, TS>(fb, blkh(k - 1, 4), w, lane, 0, NB);
-          pre_load(pvi, in, jb.ldin, k + 1);
-        }
-        if (k >= 1) put_mid(W1, (int64_t)(k - 1) * NB);
-        __syncthreads();
-        cx<R>* tmp = W2;
-        W2 = W1;
-        W1 = V;
-        V = tmp;
-      }
-      put_mid(W1, (int64_t)(K - 1) * NB);
-      __syncthreads();
-      // ---------------------------------------------------------- H backward (L^H)
-      // top = Q^H u_k - M^H carry from u_k and the carry in LDS; then
-      // x_win = P^T [top ; carry], taken row by row through the inverse
-      // permutation: window row si[d] lands on row d, rows d >= NB leave for the
-      // output and rows d < NB form the next carry in the slot w_k held, and
-      // w_{k-1} goes to the slot of the old carry.
-      cx<R>* Cb = S;           // carry: window bottom
-      cx<R>* Wk = S + SL;      // w_k, then the next carry
-      cx<R>* Vt = S + 2 * SL;  // top of the window after the step
-      zero_slots(Cb, 1);
-      {
-        TileR f0;
-        tile_issue(f0, mid, jb.ldmid, (int64_t)(K - 1) * NB);
-        tile_store(f0, Wk, (int64_t)(K - 1) * NB);
-      }
-      load_perm(K - 1);
-      // fa = M^H, fc = Q^H
-      if (PREF) frag_load<R, NB, true, const cx<R>*, TS>(fa, blkh(K - 1, 1), w, lane, 0, NB);
-      if (PREF) frag_load<R, NB, true, const cx<R>*, TS>(fc, blkh(K - 1, 0), w, lane, 0, NB);
-      __syncthreads();
-      for (int k = K - 1; k >= 0; --k) {
-        if (!PREF) frag_load<R, NB, true, const cx<R>*, TS>(fc, blkh(k, 0), w, lane, 0, NB);
-        acc.zero();
-        frag_mma<R, NB, NC, true, false>(acc, fc, Wk, LDT, nullptr, cb0, lane, 0, NB);
-        if (!PREF) frag_load<R, NB, true, const cx<R>*, TS>(fa, blkh(k, 1), w, lane, 0, NB);
-        frag_mma<R, NB, NC, true, true>(acc, fa, Cb, LDT, nullptr, cb0, lane, 0, NB);
-        TileR fw;
-        PermPre pnext;
-        if (k > 0) {
-          tile_issue(fw, mid, jb.ldmid, (int64_t)(k - 1) * NB);
-          perm_issue(pnext, k - 1);
-          if (PREF) frag_load<R, NB, true, const cx<R>*, TS>(fa, blkh(k - 1, 1), w, lane, 0, NB);
-          if (PREF) frag_load<R, NB, true, const cx<R>*, TS>(fc, blkh(k - 1, 0), w, lane, 0, NB);
-        }
-        acc_to_lds(acc, Vt, LDT, nullptr, w, cb0, lane);
-        __syncthreads();
-        {
-          cx<R> carry[RF], leave[RF];
-  #pragma unroll
-          for (int q = 0; q < RF; ++q) {
-            const int r = erow(q), col = ecol(q);
-            const int ic = si[r], il = si[NB + r];
-            carry[q] = ic < NB ? Vt[ic * LDT + col] : Cb[(ic - NB) * LDT + col];
-            leave[q] = il < NB ? Vt[il * LDT + col] : Cb[(il - NB) * LDT + col];
-          }
-  #pragma unroll
-          for (int q = 0; q < RF; ++q) Wk[erow(q) * LDT + ecol(q)] = carry[q];
-          emit_vals(leave, (int64_t)k * NB + NB);
-        }
-        __syncthreads();
-        if (k > 0) {
-          tile_store(fw, Cb, (int64_t)(k - 1) * NB);
-          perm_store(pnext);
-        }
-        cx<R>* tmp = Cb;
-        Cb = Wk;
-        Wk = tmp;
-        __syncthreads();
-      }
-      emit_tile(Cb, 0);
+      const int s = s2;
+      s2 = s1;
+      s1 = sv;
+      sv = s;
     }
+    // ---------------------------------------------------------- H backward (L^H)
+    // top = Q^H u_k - M^H carry; x_win = P^T [top ; carry]: rows below NB are
+    // the next carry (slot 0), the others leave (slot 1); u_k in slot 2
+    put_own(0, zero);
+    E pm[NC][4];
+    gtile(pm, mid, jb.ldmid, K - 1);
+    int pv = perm_get(K - 1);
+    start(blkh(K - 1, 0), true);
+    conv(pm, rowok(K - 1), x);
+    put_own(2, x);
+    perm_put(pv);
+    __syncthreads();
+    for (int k = K - 1; k >= 0; --k) {
+      const bool leaves = k + 1 < K;
+      if (jb.add && leaves) gtile(old, out, jb.ldout, k + 1);
+      gtile(pm, mid, jb.ldmid, k > 0 ? k - 1 : 0);
+      pv = perm_get(k > 0 ? k - 1 : 0);
+      acc.zero();
+      step(acc, blkh(k, 0), blkh(k, 1), blkh(k > 0 ? k - 1 : k, 0), b_slot(2), b_slot(0), true,
+           false, none);
+      E cr[NC][4];
+      get_own(0, cr);
+      const int to = spo[row], co = spo[NB + row];
+      __syncthreads();
+      acc_get(acc, x);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        lput(win(to, c), win_sw(to), x[c]);
+        lput(win(co, c), win_sw(co), cr[c]);
+      }
+      conv(pm, true, x);
+      put_own(2, x);
+      perm_put(pv);
+      __syncthreads();
+      if (leaves) {
+        get_own(1, x);
+        emit(x, old, k + 1);
+      }
+    }
+    if (jb.add) gtile(old, out, jb.ldout, 0);
+    get_own(0, x);
+    emit(x, old, 0);
   }
 }
 
-
-template <typename R, int NB, int T, bool PREF, int NC, int OCC, bool STR = false>
+template <typename R, int NB, int NC>
 int launch_nb(const cx<R>* mats, const cx<R>* matsT, const int16_t* perm, int64_t n, int njobs,
               const SolveJob* jobs_dev, hipStream_t st, const int32_t* gate) {
   const int K = (int)((n + NB - 1) / NB);
-  size_t smem = solve_lds_bytes(NB, T, sizeof(cx<R>));
-  (void)hipFuncSetAttribute((const void*)k_band_solve<R, NB, T, PREF, NC, OCC, STR>,
+  const size_t smem = solve_lds_bytes(NB, 16 * NC, sizeof(cx<R>));
+  (void)hipFuncSetAttribute((const void*)k_band_solve<R, NB, NC>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   (void)hipGetLastError();
   for (int j0 = 0; j0 < njobs; j0 += 1 << 20) {
     int nj = njobs - j0 < (1 << 20) ? njobs - j0 : (1 << 20);
     int grid = 8 * ((nj + 7) / 8);
-    k_band_solve<R, NB, T, PREF, NC, OCC, STR><<<grid, NB * 4 * (T / (16 * NC)), smem, st>>>(
-        mats, matsT, perm, n, K, jobs_dev + j0, nj, gate);
+    k_band_solve<R, NB, NC><<<grid, NB * 4, smem, st>>>(mats, matsT, perm, n, K, jobs_dev + j0,
+                                                        nj, gate);
     FB_HIP(hipGetLastError());
   }
   return 0;
 }
 
-template <typename R, int T, bool PREF, int NC, int OCC = 1, bool STR = false>
+template <typename R, int NC>
 int launch_t(const cx<R>* mats, const cx<R>* matsT, const int16_t* perm, int64_t n, int nb,
              int njobs, const SolveJob* jobs_dev, hipStream_t st, const int32_t* gate) {
   switch (nb) {
-    case 16: return launch_nb<R, 16, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 32: return launch_nb<R, 32, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 48: return launch_nb<R, 48, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 64: return launch_nb<R, 64, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 80: return launch_nb<R, 80, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 96: return launch_nb<R, 96, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 112: return launch_nb<R, 112, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    case 128: return launch_nb<R, 128, T, PREF, NC, OCC, STR>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
-    default: return FB_ERR_INTERNAL;
+    case 16: return launch_nb<R, 16, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+    case 32: return launch_nb<R, 32, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+    case 48: return launch_nb<R, 48, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+    case 64: return launch_nb<R, 64, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+    default: break;
   }
+  if constexpr (NC == 1) {  // wider blocks take 16 columns (residual groups)
+    switch (nb) {
+      case 80: return launch_nb<R, 80, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+      case 96: return launch_nb<R, 96, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+      case 112: return launch_nb<R, 112, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+      case 128: return launch_nb<R, 128, NC>(mats, matsT, perm, n, njobs, jobs_dev, st, gate);
+      default: break;
+    }
+  }
+  return FB_ERR_INTERNAL;
 }
 
-// every (tile width, prefetch, tiles per wave, register cap) variant of one
-// precision; in complex64, two tiles per wave ask for two waves per SIMD,
-// which without the cap the compiler exceeds with accumulation registers
+// tile: columns per job
 template <typename R>
-int launch_variant(int variant, const cx<R>* mats, const cx<R>* matsT, const int16_t* perm,
-                   int64_t n, int nb, int njobs, const SolveJob* jobs_dev, hipStream_t st,
-                   const int32_t* gate) {
-  // complex128 fragments are twice as wide: capped at two waves they spill
-  constexpr int kOcc2 = sizeof(R) == 4 ? 2 : 1;
-  // streamed products (8, 9): fragments no longer fill the registers
-  constexpr int kOccS = 1;
-  switch (variant) {
-    case 0: return launch_t<R, 16, false, 1>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 1: return launch_t<R, 16, true, 1>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 2: return launch_t<R, 32, false, 1>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 3: return launch_t<R, 32, true, 1>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 4: return launch_t<R, 32, false, 2, kOcc2>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 5: return launch_t<R, 32, true, 2, kOcc2>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 6: return launch_t<R, 16, false, 1, 3>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 7: return launch_t<R, 16, true, 1, 3>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 8: return launch_t<R, 16, false, 1, kOccS, true>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    case 9: return launch_t<R, 32, false, 1, kOccS, true>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
-    default: return FB_ERR_INTERNAL;
-  }
+int launch_tiles(int tile, const cx<R>* mats, const cx<R>* matsT, const int16_t* perm, int64_t n,
+                 int nb, int njobs, const SolveJob* jobs_dev, hipStream_t st,
+                 const int32_t* gate) {
+  if (tile == 16)
+    return launch_t<R, 1>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
+  if (tile == 32)
+    return launch_t<R, 2>(mats, matsT, perm, n, nb, njobs, jobs_dev, st, gate);
+  return FB_ERR_INTERNAL;
 }
 
 }  // namespace fb

@@ -4,27 +4,20 @@
 
 namespace fb {
 
-// variant v: tile width (16 or 32 right-hand sides), whether the factor
-// fragments of the next block product are prefetched into registers, how
-// many 16-column tiles one wave computes (2 for v = 4, 5, with registers
-// capped for two waves per SIMD in complex64), and for v = 6, 7 (16-column tiles)
-// registers capped for three waves per SIMD; v = 8, 9 (16- and 32-column
-// tiles) stream their factor fragments chunk by chunk instead
+// variant v: the tile width (right-hand sides per job).  Two kernels exist, v =
+// 0 and v = 2; the other numbers are choices that older tune files may hold
+// and stand for the kernel of their tile width.
 constexpr int kNumVariants = 10;
 inline int variant_tile(int v) { return ((v >= 2 && v < 6) || v == 9) ? 32 : 16; }
-inline bool variant_prefetch(int v) { return (v & 1) != 0; }
-inline int variant_nc(int v) { return (v == 4 || v == 5) ? 2 : 1; }
-inline bool variant_streamed(int v) { return v >= 8; }
-// a streamed variant is chosen only when it takes under this fraction of the
-// best other variant's time
-constexpr float kStreamedMargin = 0.97f;
-// dynamic LDS of the block-solve kernel: the block's permutation and its
-// inverse (2 NB entries each) and three NB x T slots of the factors' element
-// type with rows padded to T + 1
+constexpr int kTimedVariants[2] = {0, 2};
+// dynamic LDS of the block-solve kernel: three NB x T slots of the factors'
+// element type, the block's permutation (2 NB window rows) and the gather
+// order of its first NB rows (16-bit LDS offsets)
 inline size_t solve_lds_bytes(int nb, int t, size_t elem) {
-  return ((4 * (size_t)nb * sizeof(int) + 15) & ~(size_t)15) + (size_t)3 * nb * (t + 1) * elem;
+  return (size_t)3 * nb * t * elem + (size_t)3 * nb * 2;
 }
 bool variant_fits(size_t rsize, int nb, int v);
+// the chosen variant, or -1
 int tuned_variant(size_t rsize, int nb);
 void set_tuned_variant(size_t rsize, int nb, int v);
 

@@ -37,10 +37,7 @@ int tuned_variant(size_t rsize, int nb) {
     auto it = table().find({(int)rsize, nb});
     if (it != table().end() && variant_fits(rsize, nb, it->second)) return it->second;
   }
-  // untuned default: 32-wide tiles; prefetch where the registers allow it
-  int v = rsize == 4 ? 3 : 2;
-  while (v > 0 && !variant_fits(rsize, nb, v)) v -= 2;
-  return v;
+  return -1;
 }
 
 void set_tuned_variant(size_t rsize, int nb, int v) {
@@ -83,7 +80,7 @@ int autotune_impl(const fb_band* B, int nsys, int m, const char* path, int32_t* 
   int best = -1;
   float best_ms = 0.f;
   std::vector<std::pair<int, float>> timed;
-  for (int v = 0; v < kNumVariants; ++v) {
+  for (int v : kTimedVariants) {
     if (!variant_fits(sizeof(R), nb, v)) continue;
     const int tile = variant_tile(v);
     std::vector<SolveJob> jobs;
@@ -105,12 +102,12 @@ int autotune_impl(const fb_band* B, int nsys, int m, const char* path, int32_t* 
         }
     FB_HIP(hipMemcpyAsync(jobs_dev, jobs.data(), sizeof(SolveJob) * jobs.size(),
                           hipMemcpyHostToDevice, st));
-    set_tuned_variant(sizeof(R), nb, v);
-    FB_TRY(launch_solve_jobs<R>(f.mats, f.matsT, f.perm, bd.n, bd.b, (int)jobs.size(), jobs_dev, 0.0, st));
+    FB_TRY(launch_solve_jobs<R>(f.mats, f.matsT, f.perm, bd.n, bd.b, tile,
+                                (int)jobs.size(), jobs_dev, 0.0, st));
     FB_HIP(hipEventRecord(e0, st));
     for (int rep = 0; rep < 2; ++rep)
-      FB_TRY(launch_solve_jobs<R>(f.mats, f.matsT, f.perm, bd.n, bd.b, (int)jobs.size(), jobs_dev, 0.0,
-                                  st));
+      FB_TRY(launch_solve_jobs<R>(f.mats, f.matsT, f.perm, bd.n, bd.b, tile,
+                                  (int)jobs.size(), jobs_dev, 0.0, st));
     FB_HIP(hipEventRecord(e1, st));
     FB_HIP(hipEventSynchronize(e1));
     float ms = 0.f;
@@ -120,23 +117,11 @@ int autotune_impl(const fb_band* B, int nsys, int m, const char* path, int32_t* 
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  // The streamed variants hold one wave per SIMD: on a launch with fewer
-  // workgroups than this full-batch problem (one slice at a time) they hide
-  // less latency, so one wins only by a clear margin over the best of the rest.
-  int best_s = -1;
-  float best_s_ms = 0.f;
-  for (const auto& tv : timed) {
-    int& b = variant_streamed(tv.first) ? best_s : best;
-    float& b_ms = variant_streamed(tv.first) ? best_s_ms : best_ms;
-    if (b < 0 || tv.second < b_ms) {
-      b = tv.first;
-      b_ms = tv.second;
+  for (const auto& tv : timed)
+    if (best < 0 || tv.second < best_ms) {
+      best = tv.first;
+      best_ms = tv.second;
     }
-  }
-  if (best_s >= 0 && (best < 0 || best_s_ms < kStreamedMargin * best_ms)) {
-    best = best_s;
-    best_ms = best_s_ms;
-  }
   if (best < 0) return FB_ERR_INTERNAL;
   set_tuned_variant(sizeof(R), nb, best);
   if (chosen) *chosen = best;

@@ -157,7 +157,7 @@ extern "C" int band_inertia(const fb_band* B, int32_t nshift, const double* shif
 
 namespace fb {
 
-// Largest number of tiles refined together (bounds the residual buffers).
+// Blocks of tile complex128 columns that the residual buffer may hold.
 size_t ir_wave_jobs(int64_t n, int tile) {
   const size_t cap = (size_t)8 << 30;
   size_t per = (size_t)n * tile * sizeof(c128);
@@ -171,11 +171,14 @@ void carve_refine(Arena& ar, const Band& bd, int tile, int max_jobs, bool ir, bo
   rb.gcols = residual_cols(block_size(bd.b));  // >= tile (variant_fits)
   rb.cap_jobs = std::max(max_jobs, 1);
   rb.jobs_dev = ar.take<SolveJob>(rb.cap_jobs);
-  rb.wave = need_res ? std::min<size_t>(ir_wave_jobs(bd.n, rb.gcols), (size_t)rb.cap_jobs) : 0;
+  // the buffer is sized in complex128 columns (callers' slice and pair counts
+  // follow from its size) and holds complex64 residuals: twice the groups
+  const size_t blocks = std::min<size_t>(ir_wave_jobs(bd.n, rb.gcols), (size_t)rb.cap_jobs);
+  rb.wave = need_res ? std::min<size_t>(2 * blocks, (size_t)rb.cap_jobs) : 0;
   // every group has a residual job; a group's corrections are its tiles
   rb.rjobs_dev = need_res ? ar.take<ResJob>(rb.cap_jobs) : nullptr;
   rb.cjobs_dev = ir ? ar.take<SolveJob>(rb.cap_jobs) : nullptr;
-  rb.rbuf = need_res ? ar.take<c128>(rb.wave * (size_t)bd.n * rb.gcols) : nullptr;
+  rb.rbuf = need_res && ir ? ar.take<c64>(2 * blocks * (size_t)bd.n * rb.gcols) : nullptr;
   rb.part = need_res ? ar.take<double>(residual_part_doubles(bd.n, (int)rb.wave)) : nullptr;
   rb.ratio = need_res ? ar.take<double>(rb.cap_jobs) : nullptr;
   rb.flag = need_res ? ar.take<int32_t>(rb.cap_jobs) : nullptr;
@@ -214,6 +217,7 @@ int refine_prepare(const Band& bd, const std::vector<SolveJob>& jobs,
   plan.maxpass = ir ? ir_max : 0;
   if (njobs == 0) return 0;
   if (njobs > rb.cap_jobs) return FB_ERR_INTERNAL;
+  if (ir && sizeof(cx<R>) != sizeof(*rb.rbuf)) return FB_ERR_INTERNAL;
   FB_HIP(hipMemcpyAsync(rb.jobs_dev, jobs.data(), sizeof(SolveJob) * njobs, hipMemcpyHostToDevice, st));
   for (const SolveJob& jb : jobs) plan.cols += jb.ncol;
   if (!need_res) return 0;
@@ -246,8 +250,8 @@ int refine_prepare(const Band& bd, const std::vector<SolveJob>& jobs,
     const SolveJob& l = jobs[groups[g].second];
     ResJob& r = rj[g];
     r.x = f.out;
-    r.y = f.in;
-    r.r = rb.rbuf + ((size_t)g % rb.wave) * (size_t)bd.n * rb.gcols - (int64_t)f.col0 * bd.n;
+    r.y = (const c128*)f.in;
+    r.r = ir ? rb.rbuf + ((size_t)g % rb.wave) * (size_t)bd.n * rb.gcols : nullptr;
     r.ldx = f.ldout;
     r.ldy = f.ldin;
     r.ldr = bd.n;
@@ -260,10 +264,11 @@ int refine_prepare(const Band& bd, const std::vector<SolveJob>& jobs,
     if (ir)
       for (int i = groups[g].first; i <= groups[g].second; ++i) {
         SolveJob c = jobs[i];
-        c.in = r.r;
-        c.mid = r.r;
+        // the group's block starts at its first column
+        c.in = (const cx<R>*)r.r - (int64_t)f.col0 * bd.n;
+        c.mid = (cx<R>*)r.r - (int64_t)f.col0 * bd.n;
         c.ldin = bd.n;
-        c.ldmid = bd.n * (int64_t)(sizeof(c128) / sizeof(cx<R>));
+        c.ldmid = bd.n;
         c.add = 1;
         c.grp = g;
         cj.push_back(c);
@@ -291,7 +296,7 @@ int refine_launch(const Band& bd, const cx<R>* mats, const cx<R>* matsT, const i
     for (int g = 0; g < nw; ++g) wcols += plan.gcols[w0 + g];
     RefineCtl ctl{nullptr, rb.flag, rb.ratio, rb.npass, 0, plan.maxpass, plan.ir ? 1 : 0,
                   plan.ir_tol};
-    FB_TRY(launch_residual_jobs(bd, nw, rb.rjobs_dev + w0, rb.part, ctl,
+    FB_TRY(launch_residual_jobs<cx<R>>(bd, nw, rb.rjobs_dev + w0, rb.part, ctl,
                                 resid_flops(bd.n, bd.b, wcols), st));
     for (int pass = 1; pass <= plan.maxpass; ++pass) {
       // gated launches: their work is added once the passes are known
@@ -300,7 +305,7 @@ int refine_launch(const Band& bd, const cx<R>* mats, const cx<R>* matsT, const i
                                   rb.cjobs_dev + plan.cj_off[wi], 0.0, st, rb.flag));
       ctl.gate = rb.flag;
       ctl.pass = pass;
-      FB_TRY(launch_residual_jobs(bd, nw, rb.rjobs_dev + w0, rb.part, ctl, 0.0, st));
+      FB_TRY(launch_residual_jobs<cx<R>>(bd, nw, rb.rjobs_dev + w0, rb.part, ctl, 0.0, st));
     }
   }
   return 0;

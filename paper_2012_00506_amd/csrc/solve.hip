@@ -72,10 +72,11 @@ template int solve_tile<double>(int, size_t);
 // r = y - (zz x - B x) in FP64 for the columns of a job (zz = z for A x = y,
 // conj(z) for A^H x = y), with B in block-tridiagonal form:
 // (B x)_k = B(k,k-1) x_{k-1} + B(k,k) x_k + B(k,k+1) x_{k+1}, each an NB x NB
-// by NB x T product on f64 MFMA (three real products per complex one), one
-// wave per 16 x 16 output tile.  x blocks roll through three LDS slots and a
-// fourth holds y_k, then r_k; tiles enter and leave global memory with thread
-// e on row e % NB, column e / NB, so that a wave moves whole column runs.
+// by NB x 16 product on f64 MFMA (three real products per complex one),
+// wave w computing rows 16 w .. 16 w + 15.  As in the solves, tiles are
+// computed transposed: y and r move between global memory and the
+// accumulators' layout in runs of 256 bytes; x blocks roll through a ring of
+// LDS slots.
 //
 // A wave's share of the three products is a fixed list of 2 NB/16 + 1
 // chunks of 16 B columns (the triangles of B(k,k-1) and B(k,k+1) outside
@@ -83,158 +84,175 @@ template int solve_tile<double>(int, size_t);
 // ahead of the MFMAs that use them, across block rows and barriers, so that
 // no product waits for its first fragment.  The blocks B(0,-1) and
 // B(K-1,K) are zero, as are the x slots beyond the ends, so every block row
-// runs the same list.  Per (job, column): sum |r|^2 and sum |y|^2.
-template <int NB, int T>
-__global__ void __launch_bounds__(NB * 4 * (T / 16))
+// runs the same list.  Per (job, column): sum |r|^2 and sum |y|^2.  r (null:
+// not kept) is stored in the type RT that the correction solves compute in.
+//
+// What bounds it: the FP64 MFMAs (6 (2 b + 16) n flop per column at 72
+// TFLOP/s), then B's fragments from L2, a kilobyte per three MFMAs and wave.
+// n = 16384, 64 system-directions: b = 64, 1400 columns 28.6 -> 21.1 ms (MFMA
+// alone 15.7), b = 128, 576 columns 18.5 -> 16.6 (13.5), against 32-column
+// workgroups that staged y and r through LDS, one to a CU.
+// Slots of the x ring: three where workgroups share a CU (with registers for
+// three waves per SIMD: one chunk of B ahead); four, which save a barrier per
+// block row, for blocks of 112 and 128 rows, which have a CU to themselves (b =
+// 128: 16.6 ms against 17.4 with three).
+constexpr int residual_slots(int nb) { return nb <= 96 ? 3 : 4; }
+
+template <int NB, typename RT>
+__global__ void __launch_bounds__(NB * 4, NB <= 96 ? 3 : 2)
 k_shift_residual(const c128* __restrict__ Bblk, int64_t n, int K, const ResJob* __restrict__ jobs,
                  int njobs, double* __restrict__ part, const int32_t* __restrict__ gate) {
-  constexpr int LDT = T + 1;    // LDS row of a slot
-  constexpr int SL = NB * LDT;  // one slot
-  constexpr int NTH = NB * 4 * (T / 16);
-  constexpr int RX = NB * T / NTH;  // tile elements per thread
   constexpr int NRW = NB / 16;
-  constexpr int L = 2 * NRW + 1;    // chunks per block row and wave
-  // chunks of fragments in flight: two where the registers hold them
-  // without spilling (checked per block size), else one
-  constexpr int RD = (NB <= 32 || NB == 64) ? 2 : 1;
+  constexpr int L = 2 * NRW + 1;  // chunks per block row and wave
+  constexpr int NS = residual_slots(NB);
+  constexpr int RD = NS == 3 ? 1 : 2;
+  constexpr int SUB = residual_cols(NB) / 16;  // workgroups per job
   extern __shared__ __align__(16) char lds_raw[];
-  c128* X = reinterpret_cast<c128*>(lds_raw);  // 3 slots of x blocks
-  c128* Yr = X + 3 * SL;                       // y_k, overwritten by r_k
-  const int job = remap_job(blockIdx.x, njobs);
-  if (job >= njobs) return;
+  c128* X = reinterpret_cast<c128*>(lds_raw);  // NS slots of NB rows of 16 columns
+  const int wg = remap_job(blockIdx.x, njobs * SUB);
+  if (wg >= njobs * SUB) return;
+  const int job = wg / SUB, cs = 16 * (wg % SUB);
   const ResJob jb = jobs[job];
+  const int ncol = jb.ncol - cs;
+  if (ncol <= 0) return;
   if (gate && !gate[jb.grp]) return;  // the group has finished refining
-  const c128* jx = jb.x;
-  const c128* jy = jb.y;
-  c128* jr = jb.r;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int w = __builtin_amdgcn_readfirstlane(wv % NRW);
-  const int cb0 = __builtin_amdgcn_readfirstlane(16 * (wv / NRW));
-  const int c0 = jb.col0;
-  const int nc = jb.ncol;
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int li = lane & 15, kq = lane >> 4;
+  const int row = 16 * w + li;  // the lane's block row
   const size_t bb = (size_t)NB * NB;
   const c128 zz = jb.dir ? mk(jb.z.x, -jb.z.y) : jb.z;
-  const int kq = lane >> 4;
-  const int col = cb0 + (lane & 15);
-  // chunk i of the list: product p (0: B(k,k-1), 1: B(k,k), 2: B(k,k+1))
-  // over B columns 16 ch .. 16 ch + 15
-  const int n0 = NRW - w;  // chunks of product 0
-  auto chunk_p = [&](int i) { return i < n0 ? 0 : (i < n0 + NRW ? 1 : 2); };
-  auto chunk_c = [&](int i) { return i < n0 ? w + i : (i < n0 + NRW ? i - n0 : i - n0 - NRW); };
-  // fragment q of a chunk: B[16 w + lane % 16][16 ch + 4 q + lane / 16]
+  const c128* jx = jb.x + (int64_t)(jb.col0 + cs) * jb.ldx;
+  const c128* jy = jb.y + (int64_t)(jb.col0 + cs) * jb.ldy;
+  RT* jr = (RT*)jb.r + (int64_t)cs * jb.ldr;
+  // Chunk i of the list: B columns 16 (w + i) .. of [B(k,k-1) B(k,k) B(k,k+1)],
+  // which lie one after the other, and the same rows of [x_{k-1}; x_k;
+  // x_{k+1}], the slots taken as one ring of NS NB rows.  Fragment q:
+  // B[16 w + lane % 16][16 (w + i) + 4 q + lane / 16].
   struct Ch {
     c128 a[4];
   };
-  const c128* Brow = Bblk + (size_t)(kq * NB + 16 * w + (lane & 15));
   auto cload = [&](Ch& f, int k, int i) {
-    const c128* A = Brow + ((size_t)k * 3 + chunk_p(i)) * bb + (size_t)(16 * chunk_c(i)) * NB;
+    const c128* A = Bblk + (size_t)k * 3 * bb + (size_t)(16 * (w + i)) * NB;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) f.a[q] = gld(A + (size_t)(4 * q) * NB);
+    for (int q = 0; q < 4; ++q) f.a[q] = gld(A + 4 * q * NB + (kq * NB + row));
   };
-  // tile element q of this thread: row e % NB, column e / NB (one column
-  // per wave and q)
-  auto erow = [&](int q) { return (t + q * NTH) % NB; };
-  auto ecol = [&](int q) { return (t + q * NTH) / NB; };
-  auto ok = [&](int k, int q) {
-    const int64_t i = (int64_t)k * NB + erow(q);
-    return k < K && i < n && ecol(q) < nc;
-  };
-  // branch-free loads (clamped address, zeroed when stored), issued one
-  // block row ahead so that their latency overlaps the products
-  auto tissue = [&](c128* v, const c128* base, int64_t ld, int k) {
+  // tiles in accumulator order: element r is column kq + 4 r of the lane's
+  // row.  Columns beyond ncol read the first one (never stored).
+  auto gtile = [&](c128 (&v)[4], const c128* base, int64_t ld, int k) {
+    const int64_t i = (int64_t)k * NB + row;
+    const c128* p0 = base + (i < n ? i : n - 1);
+    const c128* pl = p0 + kq * ld;
 #pragma unroll
-    for (int q = 0; q < RX; ++q)
-      v[q] = gld(base + (ok(k, q) ? (int64_t)(c0 + ecol(q)) * ld + (int64_t)k * NB + erow(q) : 0));
+    for (int r = 0; r < 4; ++r) v[r] = gld(kq + 4 * r < ncol ? pl + 4 * r * ld : p0);
   };
-  auto tstore = [&](const c128* v, c128* dst, int k) {
-#pragma unroll
-    for (int q = 0; q < RX; ++q) dst[erow(q) * LDT + ecol(q)] = ok(k, q) ? v[q] : mk(0.0, 0.0);
+  auto rowok = [&](int k) { return (int64_t)k * NB + row < n; };
+  auto at = [&](int slot, int r) {
+    return X + (slot * NB + row) * 16 + kq + 4 * (r ^ (li & 3));
   };
-  for (int e = t; e < SL; e += NTH) X[2 * SL + e] = mk(0.0, 0.0);  // x_{-1}
-  c128 xr[RX], yv[RX];
-  double rr[RX], yy[RX];
+  auto put = [&](int slot, const c128 (&v)[4], bool ok) {
 #pragma unroll
-  for (int q = 0; q < RX; ++q) rr[q] = yy[q] = 0.0;
+    for (int r = 0; r < 4; ++r) *at(slot, r) = mk(ok ? v[r].x : 0.0, ok ? v[r].y : 0.0);
+  };
+  double rr[4], yy[4];
+  c128 xr[4], yv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) rr[r] = yy[r] = 0.0;
+  gtile(xr, jx, jb.ldx, 0);
   Ch carry[RD];
 #pragma unroll
   for (int i = 0; i < RD; ++i) cload(carry[i], 0, i);
-  tissue(xr, jx, jb.ldx, 0);
-  tstore(xr, X, 0);
-  tissue(xr, jx, jb.ldx, 1);
-  tissue(yv, jy, jb.ldy, 0);
+  put(NS - 1, xr, false);  // x_{-1}
+  put(0, xr, rowok(0));
+  gtile(xr, jx, jb.ldx, 1);
+  gtile(yv, jy, jb.ldy, 0);
+  int sm = NS - 1, s0 = 0, sp = 1;  // slots of x_{k-1}, x_k, x_{k+1}
   for (int k = 0; k < K; ++k) {
-    tstore(xr, X + ((k + 1) % 3) * SL, k + 1);
-    tstore(yv, Yr, k);
-#pragma unroll
-    for (int q = 0; q < RX; ++q)
-      if (ok(k, q)) yy[q] += cabs2(yv[q]);
+    put(sp, xr, rowok(k + 1));
     __syncthreads();
-    if (k + 2 <= K) tissue(xr, jx, jb.ldx, k + 2);
-    if (k + 1 < K) tissue(yv, jy, jb.ldy, k + 1);
-    const c128* Xk = X + (k % 3) * SL;
-    const c128* Sp[3] = {X + ((k + 2) % 3) * SL, Xk, X + ((k + 1) % 3) * SL};
-    const bool more = k + 1 < K;
-    // (B x)_k over the chunk list, then r = y - zz x + B x
+    gtile(xr, jx, jb.ldx, k + 2);
+    const int kn = k + 1 < K ? k + 1 : k;
+    auto bload = [&](c128 (&bv)[4], int i) {
+      int g = sm * NRW + w + i;
+      g -= g >= NS * NRW ? NS * NRW : 0;
+      const c128* b = X + g * 256 + (kq * 16 + (li ^ (kq << 2)));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bv[q] = b[4 * q * 16];
+    };
     Acc<double, 1> acc;
     acc.zero();
     Ch buf[L + RD];
+    c128 bv[2][4];
 #pragma unroll
     for (int i = 0; i < RD; ++i) buf[i] = carry[i];
+    bload(bv[0], 0);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       if (i + RD < L)
         cload(buf[i + RD], k, i + RD);
-      else if (more)
-        cload(buf[i + RD], k + 1, i + RD - L);
-      const int p = chunk_p(i), ch = chunk_c(i);
-      const c128* bp = (p == 0 ? Sp[0] : (p == 1 ? Sp[1] : Sp[2])) + (16 * ch + kq) * LDT + col;
-      c128 bv[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) bv[q] = bp[4 * q * LDT];
+      else
+        cload(buf[i + RD], kn, i + RD - L);
+      if (i + 1 < L) bload(bv[(i + 1) & 1], i + 1);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const double ar = buf[i].a[q].x, ai = buf[i].a[q].y;
-        acc.p1[0] = MF<double>::mma(ar, bv[q].x, acc.p1[0]);
-        acc.p2[0] = MF<double>::mma(ai, bv[q].y, acc.p2[0]);
-        acc.p3[0] = MF<double>::mma(ar + ai, bv[q].x + bv[q].y, acc.p3[0]);
+        const c128 b = bv[i & 1][q];
+        acc.p1[0] = MF<double>::mma(b.x, ar, acc.p1[0]);
+        acc.p2[0] = MF<double>::mma(b.y, ai, acc.p2[0]);
+        acc.p3[0] = MF<double>::mma(b.x + b.y, ar + ai, acc.p3[0]);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int i = 0; i < RD; ++i) carry[i] = buf[L + i];
+    const bool ok = rowok(k);
+    c128 rv[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int row = 16 * w + MF<double>::row(lane, r);
-      c128* p = Yr + row * LDT + col;
-      *p = *p - zz * Xk[row * LDT + col] + acc.get(0, r);
+      const c128* xp = at(s0, r);
+      const c128 xo = mk(xp->x, xp->y);
+      const c128 y = mk(ok ? yv[r].x : 0.0, ok ? yv[r].y : 0.0);
+      const c128 v = y - zz * xo + acc.get(0, r);
+      yy[r] += cabs2(y);
+      rr[r] += cabs2(v);
+      rv[r] = v;
     }
-    __syncthreads();
+    if (NS == 3) __syncthreads();  // before x_{k+2} takes the slot of x_{k-1}
+    gtile(yv, jy, jb.ldy, k + 1);
+    if (jb.r) {
+      RT* pl = jr + ((int64_t)k * NB + row) + kq * jb.ldr;
+      auto st = [&](int r) { gst(pl + 4 * r * jb.ldr, ccast<decltype(RT::x)>(rv[r])); };
+      if (ncol >= 16 && (int64_t)(k + 1) * NB <= n) {
 #pragma unroll
-    for (int q = 0; q < RX; ++q) {
-      if (!ok(k, q)) continue;
-      const c128 v = Yr[erow(q) * LDT + ecol(q)];
-      gst(jr + (int64_t)(c0 + ecol(q)) * jb.ldr + (int64_t)k * NB + erow(q), v);
-      rr[q] += cabs2(v);
+        for (int r = 0; r < 4; ++r) st(r);
+      } else if (ok) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kq + 4 * r < ncol) st(r);
+      }
     }
+    sm = s0;
+    s0 = sp;
+    sp = sp + 1 < NS ? sp + 1 : 0;
   }
-  // column sums in a fixed order: per-element partial sums through LDS (the
-  // x slots are free), then one thread per column adds its NB rows
+  // column sums in a fixed order: per-row partial sums through LDS, then one
+  // thread per column adds its NB rows
   __syncthreads();
-  double* red = reinterpret_cast<double*>(X);  // 2 x T columns x NB rows
+  double* red = reinterpret_cast<double*>(X);  // 2 x 16 columns x NB rows
 #pragma unroll
-  for (int q = 0; q < RX; ++q) {
-    const int e = t + q * NTH;
-    red[e] = rr[q];
-    red[NB * T + e] = yy[q];
+  for (int r = 0; r < 4; ++r) {
+    red[(kq + 4 * r) * NB + row] = rr[r];
+    red[(16 + kq + 4 * r) * NB + row] = yy[r];
   }
   __syncthreads();
-  if (t < T) {
+  if (t < 16) {
     double sr = 0.0, sy = 0.0;
     for (int i = 0; i < NB; ++i) {
       sr += red[t * NB + i];
-      sy += red[NB * T + t * NB + i];
+      sy += red[(16 + t) * NB + i];
     }
-    part[((size_t)job * 32 + t) * 2] = sr;
-    part[((size_t)job * 32 + t) * 2 + 1] = sy;
+    part[((size_t)job * 32 + cs + t) * 2] = sr;
+    part[((size_t)job * 32 + cs + t) * 2 + 1] = sy;
   }
 }
 
@@ -267,28 +285,25 @@ size_t residual_part_doubles(int64_t n, int njobs) {
   return (size_t)njobs * 32 * 2;
 }
 
-// residual jobs carry up to 32 columns; blocks of 128 rows use 16-column
-// tiles (LDS), the others 32
-template <int NB>
+template <int NB, typename RT>
 static int launch_res_nb(const Band& bd, int njobs, const ResJob* jobs_dev, double* part,
                          const int32_t* gate, hipStream_t st) {
-  constexpr int T = NB <= 64 ? 32 : 16;
-  size_t smem = (size_t)4 * NB * (T + 1) * sizeof(c128);
-  (void)hipFuncSetAttribute((const void*)k_shift_residual<NB, T>,
+  constexpr int sub = residual_cols(NB) / 16;
+  const size_t smem = (size_t)residual_slots(NB) * NB * 16 * sizeof(c128);
+  (void)hipFuncSetAttribute((const void*)k_shift_residual<NB, RT>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   (void)hipGetLastError();
   for (int j0 = 0; j0 < njobs; j0 += 1 << 20) {
     int nj = njobs - j0 < (1 << 20) ? njobs - j0 : (1 << 20);
-    int grid = 8 * ((nj + 7) / 8);
-    k_shift_residual<NB, T><<<grid, NB * 4 * (T / 16), smem, st>>>(
-        bd.Bblk, bd.n, bd.K, jobs_dev + j0, nj, part + (size_t)j0 * 64, gate);
+    int grid = 8 * ((nj * sub + 7) / 8);
+    k_shift_residual<NB, RT><<<grid, NB * 4, smem, st>>>(bd.Bblk, bd.n, bd.K, jobs_dev + j0, nj,
+                                                         part + (size_t)j0 * 64, gate);
     FB_HIP(hipGetLastError());
   }
   return 0;
 }
 
-int residual_cols(int nb) { return nb <= 64 ? 32 : 16; }
-
+template <typename RT>
 int launch_residual_jobs(const Band& bd, int njobs, const ResJob* jobs_dev, double* part,
                          const RefineCtl& ctl, double work, hipStream_t st) {
   if (njobs <= 0) return 0;
@@ -296,14 +311,14 @@ int launch_residual_jobs(const Band& bd, int njobs, const ResJob* jobs_dev, doub
   int rc;
   const int32_t* gate = ctl.gate;
   switch (bd.nb) {
-    case 16: rc = launch_res_nb<16>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 32: rc = launch_res_nb<32>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 48: rc = launch_res_nb<48>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 64: rc = launch_res_nb<64>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 80: rc = launch_res_nb<80>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 96: rc = launch_res_nb<96>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 112: rc = launch_res_nb<112>(bd, njobs, jobs_dev, part, gate, st); break;
-    case 128: rc = launch_res_nb<128>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 16: rc = launch_res_nb<16, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 32: rc = launch_res_nb<32, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 48: rc = launch_res_nb<48, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 64: rc = launch_res_nb<64, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 80: rc = launch_res_nb<80, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 96: rc = launch_res_nb<96, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 112: rc = launch_res_nb<112, RT>(bd, njobs, jobs_dev, part, gate, st); break;
+    case 128: rc = launch_res_nb<128, RT>(bd, njobs, jobs_dev, part, gate, st); break;
     default: return FB_ERR_INTERNAL;
   }
   if (rc) return rc;
@@ -311,5 +326,10 @@ int launch_residual_jobs(const Band& bd, int njobs, const ResJob* jobs_dev, doub
   FB_HIP(hipGetLastError());
   return 0;
 }
+
+template int launch_residual_jobs<c64>(const Band&, int, const ResJob*, double*, const RefineCtl&,
+                                       double, hipStream_t);
+template int launch_residual_jobs<c128>(const Band&, int, const ResJob*, double*,
+                                        const RefineCtl&, double, hipStream_t);
 
 }  // namespace fb

@@ -12,7 +12,8 @@ struct SolveJob {
   int32_t dir;    // 0: A x = y, 1: A^H x = y
   int32_t col0;   // first column of the tile
   int32_t ncol;   // columns in the tile (<= tile width)
-  const c128* in; // right-hand sides (columns from col0)
+  const void* in; // right-hand sides (columns from col0): complex128, or the
+                  // residuals of a correction (add != 0) in the factors' type
   void* mid;      // forward-sweep intermediates in the factors' complex type,
                   // ldmid in those elements; may alias in or out column by
                   // column (same column start, ldmid = ld * 16 / element size)
@@ -23,11 +24,13 @@ struct SolveJob {
                   // says whether it still runs)
 };
 
-// r = y - A x for one tile (A = zI - B, or its conjugate transpose).
+// r = y - A x for one tile (A = zI - B, or its conjugate transpose); r, the
+// block of the tile's columns (null: not kept), is in the type of the
+// correction solves.
 struct ResJob {
   const c128* x;
   const c128* y;
-  c128* r;
+  void* r;
   int64_t ldx, ldy, ldr;
   int32_t col0, ncol, dir, grp;  // grp: index of the group in the call
   c128 z;
@@ -55,7 +58,7 @@ int solve_tile(int b, size_t tiles32);
 
 size_t residual_part_doubles(int64_t n, int njobs);
 // columns per residual job for block size nb
-int residual_cols(int nb);
+constexpr int residual_cols(int nb) { return nb <= 64 ? 32 : 16; }
 // Residual of every job (group) whose gate entry is set (all when gate is
 // null), then the refinement decision per group: ratio[g] = max over its
 // columns of ||r|| / ||y||; flag[g] = 1 when the group needs a correction
@@ -69,6 +72,8 @@ struct RefineCtl {
   int pass, max_pass, ir;
   double ir_tol;
 };
+// RT: the type of the residuals kept
+template <typename RT>
 int launch_residual_jobs(const Band& bd, int njobs, const ResJob* jobs_dev, double* part,
                          const RefineCtl& ctl, double work, hipStream_t st);
 // algorithmic flops: solve 24 n b per column (L: n b, U: 2 n b complex MACs),
@@ -108,7 +113,7 @@ struct RefineBufs {
   SolveJob* jobs_dev = nullptr;
   ResJob* rjobs_dev = nullptr;   // one per group (cap_jobs)
   SolveJob* cjobs_dev = nullptr; // correction jobs of every group
-  c128* rbuf = nullptr;          // residual blocks of one wave of groups
+  c64* rbuf = nullptr;           // residual blocks of one wave of groups (ir)
   double* part = nullptr;
   double* ratio = nullptr;       // per group
   int32_t* flag = nullptr;       // per group

@@ -1,6 +1,8 @@
 // MFMA block-solve kernel templates (instantiated per precision in
 // solve_f32.hip and solve_f64.hip).
 #pragma once
+#include <type_traits>
+
 #include "fb_internal.h"
 #include "mfma.h"
 #include "prof.h"
@@ -111,7 +113,6 @@ k_band_solve(const cx<R>* __restrict__ mats, const cx<R>* __restrict__ matsT,
           if (col_of(c, r) < ncol) gst(pl + (16 * c + colr * r) * ld, v[c][r]);
     }
   };
-  const c128* in = jb.in + (int64_t)jb.col0 * jb.ldin;
   E* mid = reinterpret_cast<E*>(jb.mid) + (int64_t)jb.col0 * jb.ldmid;
   c128* out = jb.out + (int64_t)jb.col0 * jb.ldout;
 
@@ -280,11 +281,12 @@ k_band_solve(const cx<R>* __restrict__ mats, const cx<R>* __restrict__ matsT,
   for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int r = 0; r < 4; ++r) zero[c][r] = mk<R>(0, 0);
-  if (jb.dir == 0) {
-    // ---------------------------------------------------------- N forward
-    // window = slots 0 (carry) and 1 (the block's new rows): v_k = Q z_top and
-    // the next carry z_bot - M z_top, z = P y_win
-    c128 fr[NC][4];
+  // ---------------------------------------------------------- N forward
+  // window = slots 0 (carry) and 1 (the block's new rows): v_k = Q z_top and
+  // the next carry z_bot - M z_top, z = P y_win
+  auto n_forward = [&](auto in) {
+    using I = std::remove_cv_t<std::remove_pointer_t<decltype(in)>>;
+    I fr[NC][4];
     gtile(fr, in, jb.ldin, 0);
     int pv = perm_get(0);
     start(blk(0, 0), false);
@@ -333,6 +335,47 @@ k_band_solve(const cx<R>* __restrict__ mats, const cx<R>* __restrict__ matsT,
       pv = perm_get(k + 2 < K ? k + 2 : K - 1);
       __syncthreads();
     }
+  };
+  // ---------------------------------------------------------- H forward (U^H)
+  // u_k = y_k - G1(k-1)^H u_{k-1} - G2(k-2)^H u_{k-2}; block 0 stands in for
+  // the missing ones, which meet zero slots
+  auto h_forward = [&](auto in) {
+    int s1 = 0, s2 = 1, sv = 2;
+    put_own(0, zero);
+    put_own(1, zero);
+    using I = std::remove_cv_t<std::remove_pointer_t<decltype(in)>>;
+    I fr[NC][4];
+    gtile(fr, in, jb.ldin, 0);
+    start(blkh(0, 3), true);
+    conv(fr, rowok(0), x);
+    acc_set(acc, x);
+    __syncthreads();
+    for (int k = 0; k < K; ++k) {
+      gtile(fr, in, jb.ldin, k + 1 < K ? k + 1 : k);
+      step(acc, blkh(k >= 1 ? k - 1 : 0, 3), blkh(k >= 2 ? k - 2 : 0, 4), blkh(k, 3), b_slot(s1),
+           b_slot(s2), true, true, none);
+      acc_get(acc, x);
+      put_own(sv, x);
+      E y[NC][4];
+      conv(fr, rowok(k + 1), y);
+      acc_set(acc, y);
+      gput(x, mid, jb.ldmid, k);
+      __syncthreads();
+      const int s = s2;
+      s2 = s1;
+      s1 = sv;
+      sv = s;
+    }
+  };
+  // the right-hand sides of a correction are in the factors' type
+  auto with_rhs = [&](auto f) {
+    if (jb.add)
+      f((const E*)jb.in + (int64_t)jb.col0 * jb.ldin);
+    else
+      f((const c128*)jb.in + (int64_t)jb.col0 * jb.ldin);
+  };
+  if (jb.dir == 0) {
+    with_rhs(n_forward);
     // ---------------------------------------------------------- N backward
     // x_k = v_k - G1 x_{k+1} - G2 x_{k+2}; the blocks beyond the last are
     // zero, as are the slots of x_K and x_{K+1}
@@ -363,34 +406,7 @@ k_band_solve(const cx<R>* __restrict__ mats, const cx<R>* __restrict__ matsT,
       sv = s;
     }
   } else {
-    // ---------------------------------------------------------- H forward (U^H)
-    // u_k = y_k - G1(k-1)^H u_{k-1} - G2(k-2)^H u_{k-2}; block 0 stands in for
-    // the missing ones, which meet zero slots
-    int s1 = 0, s2 = 1, sv = 2;
-    put_own(0, zero);
-    put_own(1, zero);
-    c128 fr[NC][4];
-    gtile(fr, in, jb.ldin, 0);
-    start(blkh(0, 3), true);
-    conv(fr, rowok(0), x);
-    acc_set(acc, x);
-    __syncthreads();
-    for (int k = 0; k < K; ++k) {
-      gtile(fr, in, jb.ldin, k + 1 < K ? k + 1 : k);
-      step(acc, blkh(k >= 1 ? k - 1 : 0, 3), blkh(k >= 2 ? k - 2 : 0, 4), blkh(k, 3), b_slot(s1),
-           b_slot(s2), true, true, none);
-      acc_get(acc, x);
-      put_own(sv, x);
-      E y[NC][4];
-      conv(fr, rowok(k + 1), y);
-      acc_set(acc, y);
-      gput(x, mid, jb.ldmid, k);
-      __syncthreads();
-      const int s = s2;
-      s2 = s1;
-      s1 = sv;
-      sv = s;
-    }
+    with_rhs(h_forward);
     // ---------------------------------------------------------- H backward (L^H)
     // top = Q^H u_k - M^H carry; x_win = P^T [top ; carry]: rows below NB are
     // the next carry (slot 0), the others leave (slot 1); u_k in slot 2

@@ -110,17 +110,26 @@ __global__ void __launch_bounds__(256) k_bj_norms(BJDev* __restrict__ dv, int cu
   }
 }
 
-__global__ void k_bj_norms_final(BJDev* __restrict__ dv, int nmat, double* __restrict__ out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nmat) return;
-  const BJDev d = dv[q];
-  double off = 0.0, all = 0.0;
-  for (int j = 0; j < d.mp; ++j) {
-    off += gld(d.part + 2 * j);
-    all += gld(d.part + 2 * j + 1);
+// one workgroup per matrix: the columns' sums through LDS, added in order
+__global__ void __launch_bounds__(256) k_bj_norms_final(BJDev* __restrict__ dv,
+                                                        double* __restrict__ out) {
+  __shared__ double part[2][256];
+  const BJDev d = dv[blockIdx.x];
+  const int t = threadIdx.x;
+  double sum = 0.0;
+  for (int j0 = 0; j0 < d.mp; j0 += 256) {
+    const int nj = min(256, d.mp - j0);
+    if (t < nj) {
+      part[0][t] = gld(d.part + 2 * (j0 + t));
+      part[1][t] = gld(d.part + 2 * (j0 + t) + 1);
+    }
+    __syncthreads();
+    if (t < 2)
+#pragma unroll 8
+      for (int j = 0; j < nj; ++j) sum += part[t][j];
+    __syncthreads();
   }
-  out[2 * q] = off;
-  out[2 * q + 1] = all;
+  if (t < 2) out[2 * blockIdx.x + t] = sum;
 }
 
 // -------------------------------------------------------------- pair solves
@@ -597,7 +606,7 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   for (int sw = 0; sw <= max_sweeps; ++sw) {
     k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd, cur);
     FB_HIP(hipGetLastError());
-    k_bj_norms_final<<<(nj + 63) / 64, 64, 0, st>>>(dvd, nj, norms_dev);
+    k_bj_norms_final<<<nj, 256, 0, st>>>(dvd, norms_dev);
     FB_HIP(hipGetLastError());
     FB_HIP(hipMemcpyAsync(nrm.data(), norms_dev, sizeof(double) * 2 * nj, hipMemcpyDeviceToHost, st));
     FB_HIP(hipStreamSynchronize(st));

@@ -498,8 +498,9 @@ extern "C" int planner_train_step(void* weights, void* opt_state, int32_t batch,
   float* dY = Y + nf * kH3;
   float* dZ2 = dY + nf * kH3;
   float* dZ1 = dZ2 + nf * kH2;
-  float* G = grads ? (float*)grads : dZ1 + nf * kH1;
-  float* lpart = G + kNetParams;
+  float* own = dZ1 + nf * kH1;  // kNetParams gradients, then the loss
+  float* G = grads ? (float*)grads : own;
+  float* lpart = own + kNetParams;
   float* ldev = lpart + 256;
   float *gW1 = G, *gb1 = gW1 + kH0 * kH1, *gW2 = gb1 + kH1, *gb2 = gW2 + kH1 * kH2,
         *gW3 = gb2 + kH2, *gb3 = gW3 + kH2 * kH3;

@@ -290,25 +290,45 @@ struct GemmArgs {
   int relu;
 };
 
-__global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int tiles_n = (g.N + 15) / 16;
-  const int tile = blockIdx.x * 4 + wv;
-  const int tm = tile / tiles_n, tn = tile % tiles_n;
-  if (tm * 16 >= g.M) return;
-  const int i = tm * 16 + (lane & 15), j = tn * 16 + (lane & 15), kq = 4 * (lane >> 4);
-  pl_f4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
-    pl_s4 a, b;
+// S steps of 16 in k from k0: every load of the S steps before the first use
+template <int S>
+__device__ __forceinline__ void gemm_steps(const GemmArgs& g, int i, int j, int k0, int kq,
+                                           pl_f4& acc) {
+  // elements beyond the matrices are read at their last row or column, then zero
+  const float* pa = g.A + (size_t)min(i, g.M - 1) * g.sai;
+  const float* pb = g.B + (size_t)min(j, g.N - 1) * g.sbj;
+  float av[S][4], bv[S][4];
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
     for (int v = 0; v < 4; ++v) {
-      int k = k0 + kq + v;
-      float av = (i < g.M && k < g.K) ? g.A[(size_t)i * g.sai + (size_t)k * g.sak] : 0.f;
-      float bv = (j < g.N && k < g.K) ? g.B[(size_t)k * g.sbk + (size_t)j * g.sbj] : 0.f;
-      a[v] = to_bf16(av);
-      b[v] = to_bf16(bv);
+      const int k = min(k0 + 16 * s + kq + v, g.K - 1);
+      av[s][v] = pa[(size_t)k * g.sak];
+      bv[s][v] = pb[(size_t)k * g.sbk];
+    }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    pl_s4 a, b;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const bool in = k0 + 16 * s + kq + v < g.K;
+      a[v] = to_bf16(i < g.M && in ? av[s][v] : 0.f);
+      b[v] = to_bf16(j < g.N && in ? bv[s][v] : 0.f);
     }
     acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
   }
+}
+
+// one wave: tile (tm, tn) of C
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tile, int lane) {
+  const int tiles_n = (g.N + 15) / 16;
+  const int tm = tile / tiles_n, tn = tile % tiles_n;
+  const int i = tm * 16 + (lane & 15), j = tn * 16 + (lane & 15), kq = 4 * (lane >> 4);
+  pl_f4 acc = {0.f, 0.f, 0.f, 0.f};
+  int k0 = 0;
+  for (; k0 + 240 < g.K; k0 += 256) gemm_steps<16>(g, i, j, k0, kq, acc);
+  for (; k0 + 48 < g.K; k0 += 64) gemm_steps<4>(g, i, j, k0, kq, acc);
+  for (; k0 < g.K; k0 += 16) gemm_steps<1>(g, i, j, k0, kq, acc);
   for (int r = 0; r < 4; ++r) {
     int row = tm * 16 + 4 * (lane >> 4) + r, col = tn * 16 + (lane & 15);
     if (row >= g.M || col >= g.N) continue;
@@ -320,11 +340,88 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
   }
 }
 
-static int gemm(const GemmArgs& g, hipStream_t st) {
-  int tiles = ((g.M + 15) / 16) * ((g.N + 15) / 16);
-  k_gemm_bf16<<<(tiles + 3) / 4, 256, 0, st>>>(g);
+// column sums of a rows x cols row-major array (bias gradients)
+struct ColsumArgs {
+  const float* X;
+  int rows, cols;
+  float* out;
+};
+// the loss from its nb partial sums
+struct LossArgs {
+  const float* part;
+  int nb;
+  float inv;
+  float* loss;
+};
+
+// Products that do not depend on each other, the column sums beside them and
+// the loss, in one launch: workgroups of one wave, one per 16 x 16 tile of the
+// products, then one per 64 column sums, then one for the loss.
+// What bounds it: latency.  At batch 64 a training step moves 2.5 MB and
+// multiplies 39 MF, microseconds of work in a dozen dependent launches; with
+// loads that waited for each other in every step of k and a launch per
+// product and sum a step took 145 us, now 82.
+struct MixArgs {
+  GemmArgs g[2];
+  int tiles[2];  // of the products (0: none)
+  ColsumArgs c;
+  LossArgs l;
+};
+
+__global__ void __launch_bounds__(64) k_planner_mix(MixArgs a) {
+  const int lane = threadIdx.x;
+  int id = blockIdx.x;
+  if (id < a.tiles[0]) {
+    gemm_tile(a.g[0], id, lane);
+    return;
+  }
+  id -= a.tiles[0];
+  if (id < a.tiles[1]) {
+    gemm_tile(a.g[1], id, lane);
+    return;
+  }
+  id -= a.tiles[1];
+  const int c = 64 * id + lane;
+  if (64 * id < a.c.cols) {
+    if (c >= a.c.cols) return;
+    const float* X = a.c.X + c;
+    float s = 0.f;
+    int r = 0;
+    for (; r + 32 <= a.c.rows; r += 32) {
+      float v[32];
+#pragma unroll
+      for (int q = 0; q < 32; ++q) v[q] = X[(size_t)(r + q) * a.c.cols];
+#pragma unroll
+      for (int q = 0; q < 32; ++q) s += v[q];
+    }
+    for (; r < a.c.rows; ++r) s += X[(size_t)r * a.c.cols];
+    a.c.out[c] = s;
+    return;
+  }
+  if (lane == 0 && a.l.loss) {
+    float s = 0.f;
+#pragma unroll 16
+    for (int q = 0; q < a.l.nb; ++q) s += a.l.part[q];
+    *a.l.loss = s * a.l.inv;
+  }
+}
+
+static int mix(MixArgs a, hipStream_t st) {
+  int blocks = (a.c.cols + 63) / 64 + (a.l.loss ? 1 : 0);
+  for (int q = 0; q < 2; ++q) {
+    const GemmArgs& g = a.g[q];
+    a.tiles[q] = ((g.M + 15) / 16) * ((g.N + 15) / 16);
+    blocks += a.tiles[q];
+  }
+  k_planner_mix<<<blocks, 64, 0, st>>>(a);
   FB_HIP(hipGetLastError());
   return 0;
+}
+
+static int gemm(const GemmArgs& g, hipStream_t st) {
+  MixArgs a{};
+  a.g[0] = g;
+  return mix(a, st);
 }
 
 // dY = 2 (Y - T) / (B * 64); loss partials
@@ -347,15 +444,6 @@ __global__ void k_mse_grad(const float* __restrict__ Y, const float* __restrict_
   if (threadIdx.x == 0) lpart[blockIdx.x] = red[0];
 }
 
-// column sums of a rows x cols row-major array (bias gradients)
-__global__ void k_colsum(const float* __restrict__ X, int rows, int cols, float* __restrict__ out) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += X[(size_t)r * cols + c];
-  out[c] = s;
-}
-
 __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
                        const float* __restrict__ g, int count, float lr, float b1, float b2,
                        float eps, float c1, float c2) {
@@ -367,13 +455,6 @@ __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __re
     v[e] = vv;
     w[e] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
   }
-}
-
-__global__ void k_lossfinal(const float* __restrict__ lpart, int nb, float inv, float* __restrict__ loss) {
-  if (threadIdx.x || blockIdx.x) return;
-  float s = 0.f;
-  for (int i = 0; i < nb; ++i) s += lpart[i];
-  *loss = s * inv;
 }
 
 struct Net {
@@ -509,18 +590,15 @@ extern "C" int planner_train_step(void* weights, void* opt_state, int32_t batch,
   const int lb = std::min(256, (cnt + 255) / 256);
   k_mse_grad<<<lb, 256, 0, st>>>(Y, target, dY, cnt, 1.f / (float)cnt, lpart);
   FB_HIP(hipGetLastError());
-  // W3: H2^T dY, b3: colsum dY, dZ2 = (dY W3^T) * (H2 > 0)
-  FB_TRY(gemm({kH2, kH3, batch, H2, 1, kH2, dY, kH3, 1, gW3, kH3, nullptr, nullptr, 0}, st));
-  k_colsum<<<(kH3 + 63) / 64, 64, 0, st>>>(dY, batch, kH3, gb3);
-  FB_TRY(gemm({batch, kH2, kH3, dY, kH3, 1, n.W3, 1, kH3, dZ2, kH2, nullptr, H2, 0}, st));
-  FB_TRY(gemm({kH1, kH2, batch, H1, 1, kH1, dZ2, kH2, 1, gW2, kH2, nullptr, nullptr, 0}, st));
-  k_colsum<<<(kH2 + 63) / 64, 64, 0, st>>>(dZ2, batch, kH2, gb2);
-  FB_TRY(gemm({batch, kH1, kH2, dZ2, kH2, 1, n.W2, 1, kH2, dZ1, kH1, nullptr, H1, 0}, st));
-  FB_TRY(gemm({kH0, kH1, batch, x, 1, kH0, dZ1, kH1, 1, gW1, kH1, nullptr, nullptr, 0}, st));
-  k_colsum<<<(kH1 + 63) / 64, 64, 0, st>>>(dZ1, batch, kH1, gb1);
-  FB_HIP(hipGetLastError());
-  k_lossfinal<<<1, 1, 0, st>>>(lpart, lb, 1.f / (float)cnt, ldev);
-  FB_HIP(hipGetLastError());
+  // W3: H2^T dY, b3: colsum dY, dZ2 = (dY W3^T) * (H2 > 0), and the loss
+  FB_TRY(mix({{{kH2, kH3, batch, H2, 1, kH2, dY, kH3, 1, gW3, kH3, nullptr, nullptr, 0},
+               {batch, kH2, kH3, dY, kH3, 1, n.W3, 1, kH3, dZ2, kH2, nullptr, H2, 0}},
+              {0, 0}, {dY, batch, kH3, gb3}, {lpart, lb, 1.f / (float)cnt, ldev}}, st));
+  FB_TRY(mix({{{kH1, kH2, batch, H1, 1, kH1, dZ2, kH2, 1, gW2, kH2, nullptr, nullptr, 0},
+               {batch, kH1, kH2, dZ2, kH2, 1, n.W2, 1, kH2, dZ1, kH1, nullptr, H1, 0}},
+              {0, 0}, {dZ2, batch, kH2, gb2}, {}}, st));
+  FB_TRY(mix({{{kH0, kH1, batch, x, 1, kH0, dZ1, kH1, 1, gW1, kH1, nullptr, nullptr, 0}, {}},
+              {0, 0}, {dZ1, batch, kH1, gb1}, {}}, st));
   if (!grads) {
     float* m = (float*)opt_state;
     float* v = m + kNetParams;

@@ -207,13 +207,13 @@ struct BJElem<false> {
 // What bounds it: the angles' chain of divisions and square roots on one
 // wave, and in complex arithmetic the LDS traffic of S and U beside it.  With
 // all waves waiting for the angles and two barriers a launch of 63 rounds took
-// 147 us, real or complex; now 122 us complex (three matrices of 320 columns)
-// and 87 us real.
-template <bool CPLX>
+// 147 us, real or complex; now, with U shared out over four workgroups, 95 us
+// complex (20 pairs) and 72 us real (122 and 87 us in one workgroup).
+template <bool CPLX, bool SPLIT>
 __device__ __forceinline__ int bj_pair_sweeps(char* lds, BJRot (*rot)[kBs],
                                               double (*red)[kPairThreads],
                                               const c128* __restrict__ A, int64_t base, int mp,
-                                              c128* __restrict__ U) {
+                                              c128* __restrict__ U, int part, int rlog) {
   using X = BJElem<CPLX>;
   using E = typename X::E;
   E* S = reinterpret_cast<E*>(lds);  // column-major, ld kPL
@@ -289,6 +289,9 @@ __device__ __forceinline__ int bj_pair_sweeps(char* lds, BJRot (*rot)[kBs],
     kk += kk >= e1 ? 1 : 0;
     kk += kk >= e2 ? 1 : 0;
   }
+  const int urow = SPLIT ? (part << rlog) + (lane & ((1 << rlog) - 1)) : lane;
+  // wave 0 is the one that the others wait for
+  if (w == 0) __builtin_amdgcn_s_setprio(3);
   int rotated = 0;
   for (int sw = 0; sw < kInner; ++sw) {
     // stop when the block is diagonal relative to its (non-padding) diagonal
@@ -330,32 +333,40 @@ __device__ __forceinline__ int bj_pair_sweeps(char* lds, BJRot (*rot)[kBs],
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (ro + 2 < kPb) angles(ro + 1, rot[(ro & 1) ^ 1]);
       } else {
-        // U <- U J (columns p, q), a pair per wave
-        for (int k = w - 1; k < kBs; k += kPairThreads / 64 - 1) {
+        // U <- U J (columns p, q), a lane per row of U and pair
+        const int step = SPLIT ? 64 >> rlog : 1;  // pairs per wave
+        for (int k = (w - 1) * step + (SPLIT ? lane >> rlog : 0); k < kBs;
+             k += (kPairThreads / 64 - 1) * step) {
           const int a = player(k, ro), b = player(kPb - 1 - k, ro);
           const int p = min(a, b), q = max(a, b);
           const BJRot r = o[k];
-          const E vp = Us[p * kPL + lane], vq = X::mulu(r.e, Us[q * kPL + lane]);
-          Us[p * kPL + lane] = X::minus(r.cs, vp, r.sn, vq);
-          Us[q * kPL + lane] = X::plus(r.sn, vp, r.cs, vq);
+          const E vp = Us[p * kPL + urow], vq = X::mulu(r.e, Us[q * kPL + urow]);
+          Us[p * kPL + urow] = X::minus(r.cs, vp, r.sn, vq);
+          Us[q * kPL + urow] = X::plus(r.sn, vp, r.cs, vq);
         }
       }
       __syncthreads();
     }
   }
-  for (int e = t; e < kPb * kPb; e += kPairThreads) {
-    const int k = e / kPb, jc = e % kPb;  // row-major
-    gst(U + e, X::to(Us[jc * kPL + k]));
+  if (w == 0) __builtin_amdgcn_s_setprio(0);
+  const int e1 = SPLIT ? kPb << rlog : kPb * kPb;
+  for (int e = t; e < e1; e += kPairThreads) {
+    const int k = (SPLIT ? part << rlog : 0) + e / kPb, jc = e % kPb;  // row-major
+    gst(U + k * kPb + jc, X::to(Us[jc * kPL + k]));
   }
   return rotated;
 }
 
-__global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ dv, int cur) {
+// Workgroup (K 2^(6 - rlog) + part, matrix): pair K, and of its U the rows
+// 2^rlog part .. 2^rlog (part + 1) - 1.  The workgroups of a pair repeat the
+// same rotations of S, each for its own rows of U.
+__global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ dv, int cur,
+                                                           int rlog) {
   extern __shared__ __align__(16) char lds_raw[];
   __shared__ BJRot rot[2][kBs];
   __shared__ double red[2][kPairThreads];
   const BJDev d = dv[blockIdx.y];
-  const int K = blockIdx.x;
+  const int K = blockIdx.x >> (6 - rlog), part = blockIdx.x & ((64 >> rlog) - 1);
   if (K >= d.h) return;
   const int t = threadIdx.x;
   const c128* A = (cur ? d.A[1] : d.A[0]);
@@ -364,10 +375,15 @@ __global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ d
   for (int e = t; e < kPb * kPb; e += kPairThreads)
     imag |= gld(A + (base + e / kPb) * d.mp + base + e % kPb).y != 0.0;
   c128* U = d.U + (size_t)K * kPb * kPb;
-  const int rotated = __syncthreads_or(imag)
-                          ? bj_pair_sweeps<true>(lds_raw, rot, red, A, base, d.mp, U)
-                          : bj_pair_sweeps<false>(lds_raw, rot, red, A, base, d.mp, U);
-  if (t == 0) gst(d.skip + K, rotated ? 0 : 1);
+  const bool cplx = __syncthreads_or(imag);
+  int rotated;
+  if (rlog == 6)
+    rotated = cplx ? bj_pair_sweeps<true, false>(lds_raw, rot, red, A, base, d.mp, U, 0, 6)
+                   : bj_pair_sweeps<false, false>(lds_raw, rot, red, A, base, d.mp, U, 0, 6);
+  else
+    rotated = cplx ? bj_pair_sweeps<true, true>(lds_raw, rot, red, A, base, d.mp, U, part, rlog)
+                   : bj_pair_sweeps<false, true>(lds_raw, rot, red, A, base, d.mp, U, part, rlog);
+  if (t == 0 && part == 0) gst(d.skip + K, rotated ? 0 : 1);
 }
 
 // -------------------------------------------------------------- updates
@@ -602,6 +618,11 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   FB_HIP(hipGetLastError());
   std::vector<double> nrm(2 * nj);
   int sweeps = 0, cur = 0;  // cur: which copy of A and V a round reads
+  // few pairs leave most of the chip idle: their U is then shared out over 2
+  // or 4 workgroups each, as long as every workgroup has a CU of its own (a
+  // second round of workgroups would cost more than the 18 % that it saves)
+  constexpr int kCUs = 256;
+  const int rlog = 4 * max_h * nj <= kCUs ? 4 : 2 * max_h * nj <= kCUs ? 5 : 6;
   const int upd_wgs = max_h * (max_h + 1) / 2 + max_h * (max_mp / kPb);
   for (int sw = 0; sw <= max_sweeps; ++sw) {
     k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd, cur);
@@ -618,7 +639,7 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
     // every matrix takes max_rounds rounds (a smaller one completes further
     // sweeps of its own schedule, which keeps it converging)
     for (int r = 0; r < max_rounds; ++r) {
-      k_bj_pairs<<<dim3(max_h, nj), kPairThreads, lds_pairs, st>>>(dvd, cur);
+      k_bj_pairs<<<dim3(max_h << (6 - rlog), nj), kPairThreads, lds_pairs, st>>>(dvd, cur, rlog);
       FB_HIP(hipGetLastError());
       k_bj_update<<<dim3(upd_wgs, nj), 256, lds_upd, st>>>(dvd, cur);
       FB_HIP(hipGetLastError());

@@ -42,3 +42,30 @@ def test_pairs_real_and_complex(kind, m):
     assert np.abs(np.sort(r.lam) - lam).max() <= 1e-12 * nrm
     X = r.X.cpu().numpy()
     assert np.abs(X.conj().T @ X - np.eye(m)).max() < 1e-12
+
+
+@pytest.mark.parametrize("blocks", [1, 20, 30])
+@pytest.mark.parametrize("cplx", [True, False])
+def test_shared_out_pairs(cplx, blocks):
+    """A call with few pairs shares each pair's transformation out over 4 or 2
+    workgroups, one with many does not: calls of 1, 20 and 30 equal blocks (5,
+    100 and 150 pairs), whose results are also equal to each other within a
+    call.  (Between calls they differ by rounding: the Gram matrices' sums are
+    split by the number of blocks.)"""
+    import paper_2012_00506_amd as fb
+    n, m = 400, 260
+    print(f"bjacobi shared out cplx={cplx} blocks={blocks}", flush=True)
+    ab = synth.band_matrix(n, 4, 33, cplx, -20, 20)
+    rng = np.random.default_rng(5)
+    Q = rng.standard_normal((n, m))
+    if cplx:
+        Q = Q + 1j * rng.standard_normal((n, m))
+    Q, _ = np.linalg.qr(Q)
+    out = fb.rayleigh_ritz(ab, [fb.to_colmajor(Q)] * blocks)
+    A = Q.conj().T @ oband.dense_from_band(ab) @ Q
+    lam = np.linalg.eigvalsh((A + A.conj().T) / 2)
+    X = out[0].X.cpu().numpy()
+    assert np.abs(np.sort(out[0].lam) - lam).max() <= 1e-12 * oband.norm1(ab)
+    assert np.abs(X.conj().T @ X - np.eye(m)).max() < 1e-12
+    for r in out[1:]:
+        assert np.array_equal(r.lam, out[0].lam) and bool((r.X == out[0].X).all())

@@ -39,7 +39,7 @@ struct BJDev {  // kBjDescBytes bytes
   c128* U;      // h x 64 x 64, row-major per pair: U[K][k * 64 + j] = U_K(k, j)
   int32_t* skip;// h: U of the pair is the identity
   double* part; // 2 doubles per column of A: off^2 and total^2 partial sums
-  int32_t m, mp, h, pad;
+  int32_t m, mp, h, cplx;  // cplx: an imaginary part is set in A
 };
 
 typedef double bd4 __attribute__((ext_vector_type(4)));
@@ -63,6 +63,7 @@ __global__ void k_bj_init(const JacobiJob* __restrict__ jobs, BJDev* __restrict_
   const JacobiJob jb = jobs[blockIdx.y];
   const BJDev d = dv[blockIdx.y];
   const int64_t tot = (int64_t)d.mp * d.mp;
+  bool imag = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(e / d.mp), i = (int)(e - (int64_t)j * d.mp);
@@ -73,7 +74,9 @@ __global__ void k_bj_init(const JacobiJob* __restrict__ jobs, BJDev* __restrict_
       a = mk(kPad, 0.0);
     gst(d.A[0] + e, a);
     gst(d.V[0] + e, mk(i == j ? 1.0 : 0.0, 0.0));
+    imag |= a.y != 0.0;
   }
+  if (__syncthreads_or(imag) && threadIdx.x == 0) atomicOr(&dv[blockIdx.y].cplx, 1);
 }
 
 // -------------------------------------------------------------- off-norm
@@ -372,7 +375,7 @@ __global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ d
   const c128* A = (cur ? d.A[1] : d.A[0]);
   const int64_t base = (int64_t)K * kPb;
   bool imag = false;
-  for (int e = t; e < kPb * kPb; e += kPairThreads)
+  for (int e = t; d.cplx && e < kPb * kPb; e += kPairThreads)
     imag |= gld(A + (base + e / kPb) * d.mp + base + e % kPb).y != 0.0;
   c128* U = d.U + (size_t)K * kPb * kPb;
   const bool cplx = __syncthreads_or(imag);
@@ -391,63 +394,70 @@ __global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ d
 // R = U_K^H A[K,L] U_L (R^H is the tile (L, K): A stays Hermitian);
 // workgroups from h(h+1)/2 on: the tiles (I, L) of V, V[I, L] U_L.  Each
 // 32-row and 32-column block of the result is written to its next-round
-// position.  Four waves each own a 32 x 32 quarter of a 64 x 64 x 64
-// product (2 x 2 MFMA tiles of 16 x 16, Gauss form); operand fragments are
+// position.  The columns of a tile are independent: CS workgroups take 64 /
+// CS of them each.  Four waves share them, RT x CT MFMA tiles of 16 x 16 per
+// wave (Gauss form; a real matrix takes the first of its three products, the
+// second is zero and the third equal to the first); operand fragments are
 // loaded one contraction step ahead.
-template <bool CONJA, typename FA, typename FB>
-__device__ __forceinline__ void bj_quarter(bd4 (&p1)[2][2], bd4 (&p2)[2][2], bd4 (&p3)[2][2],
-                                           FA fa, FB fb, int lk) {
+// What bounds it: the latency of the two dependent products of an A tile, at
+// the few tiles that a call has for 256 CUs.  Whole tiles took 35 us per launch
+// for two complex matrices of 640 columns and 28 us for a real one of 320; now
+// 26 (CS = 2) and 12 us (CS = 4).
+template <bool CONJA, bool CPLX, int RT, int CT, typename FA, typename FB>
+__device__ __forceinline__ void bj_products(bd4 (&p1)[RT][CT], bd4 (&p2)[RT][CT],
+                                            bd4 (&p3)[RT][CT], FA fa, FB fb, int lk) {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RT; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < CT; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) p1[a][b][r] = p2[a][b][r] = p3[a][b][r] = 0.0;
-  c128 an[2], bn[2];
+  c128 an[RT], bn[CT];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    an[q] = fa(q, lk);
-    bn[q] = fb(q, lk);
-  }
+  for (int q = 0; q < RT; ++q) an[q] = fa(q, lk);
+#pragma unroll
+  for (int q = 0; q < CT; ++q) bn[q] = fb(q, lk);
 #pragma unroll 2
   for (int kk = 0; kk < kPb; kk += 4) {
-    c128 ac[2] = {an[0], an[1]}, bc[2] = {bn[0], bn[1]};
+    double ar[RT], ai[RT], as[RT], br[CT], bi[CT], bs[CT];
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+      ar[q] = an[q].x;
+      ai[q] = CONJA ? -an[q].y : an[q].y;
+      as[q] = ar[q] + ai[q];
+    }
+#pragma unroll
+    for (int q = 0; q < CT; ++q) {
+      br[q] = bn[q].x;
+      bi[q] = bn[q].y;
+      bs[q] = bn[q].x + bn[q].y;
+    }
     if (kk + 4 < kPb) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        an[q] = fa(q, kk + 4 + lk);
-        bn[q] = fb(q, kk + 4 + lk);
-      }
-    }
-    double ar[2], ai[2], as[2], br[2], bi[2], bs[2];
+      for (int q = 0; q < RT; ++q) an[q] = fa(q, kk + 4 + lk);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      ar[q] = ac[q].x;
-      ai[q] = CONJA ? -ac[q].y : ac[q].y;
-      as[q] = ar[q] + ai[q];
-      br[q] = bc[q].x;
-      bi[q] = bc[q].y;
-      bs[q] = bc[q].x + bc[q].y;
+      for (int q = 0; q < CT; ++q) bn[q] = fb(q, kk + 4 + lk);
     }
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
+      for (int ct = 0; ct < CT; ++ct) {
         p1[rt][ct] = bj_mfma(ar[rt], br[ct], p1[rt][ct]);
-        p2[rt][ct] = bj_mfma(ai[rt], bi[ct], p2[rt][ct]);
-        p3[rt][ct] = bj_mfma(as[rt], bs[ct], p3[rt][ct]);
+        if (CPLX) {
+          p2[rt][ct] = bj_mfma(ai[rt], bi[ct], p2[rt][ct]);
+          p3[rt][ct] = bj_mfma(as[rt], bs[ct], p3[rt][ct]);
+        }
       }
   }
 }
 
-__global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv, int cur) {
-  extern __shared__ __align__(16) char lds_raw[];
-  c128* Ts = reinterpret_cast<c128*>(lds_raw);  // 64 x 64, column-major, ld kPL
-  const BJDev d = dv[blockIdx.y];
+template <bool CPLX, int CS>
+__device__ __forceinline__ void bj_update_part(const BJDev& d, int cur, c128* Ts, int wg,
+                                               int part) {
+  constexpr int RT = CS == 1 ? 2 : 1, CT = CS == 4 ? 1 : 2;
+  constexpr int NCOL = kPb / CS;
   const int h = d.h;
-  const int nA = h * (h + 1) / 2, nV = h * (d.mp / kPb);
-  const int wg = blockIdx.x;
-  if (wg >= nA + nV) return;
+  const int nA = h * (h + 1) / 2;
   const bool isA = wg < nA;
   int K, L;
   if (isA) {  // wg -> (K, L), K <= L, row by row
@@ -469,61 +479,79 @@ __global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv, int c
   const int64_t r0 = (int64_t)K * kPb, c0 = (int64_t)L * kPb;
   const int skK = isA ? gld(d.skip + K) : 1, skL = gld(d.skip + L);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int wr = w & 1, wc = w >> 1;
+  const int j0 = NCOL * part;  // the workgroup's columns of the tile
+  // the wave's rows and, within those columns, columns
+  const int wr = 16 * RT * (CS == 1 ? w & 1 : w), wc = CS == 1 ? 32 * (w >> 1) : 0;
   const int li = lane & 15, lk = lane >> 4;
-  const c128* UL = d.U + (size_t)L * kPb * kPb;
+  const c128* UL = d.U + (size_t)L * kPb * kPb + j0;
   const c128* UK = d.U + (size_t)K * kPb * kPb;
-  bd4 p1[2][2], p2[2][2], p3[2][2];
+  bd4 p1[RT][CT], p2[RT][CT], p3[RT][CT];
   auto to_lds = [&]() {
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
+      for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i = 32 * wr + 16 * rt + lk + 4 * r, j = 32 * wc + 16 * ct + li;
+          const int i = wr + 16 * rt + lk + 4 * r, j = wc + 16 * ct + li;
           const double x1 = p1[rt][ct][r], x2 = p2[rt][ct][r], x3 = p3[rt][ct][r];
-          Ts[j * kPL + i] = mk(x1 - x2, x3 - x1 - x2);
+          Ts[j * kPL + i] = CPLX ? mk(x1 - x2, x3 - x1 - x2) : mk(x1, 0.0);
         }
   };
 
   if (skL) {  // no product on the right: the tile itself
-    for (int e = t; e < kPb * kPb; e += blockDim.x) {
+    for (int e = t; e < kPb * NCOL; e += 256) {
       const int j = e / kPb, i = e % kPb;
-      Ts[j * kPL + i] = gld(Src + (c0 + j) * ld + r0 + i);
+      Ts[j * kPL + i] = gld(Src + (c0 + j0 + j) * ld + r0 + i);
     }
   } else {  // T = Src[K, L] U_L
-    bj_quarter<false>(
-        p1, p2, p3,
-        [&](int q, int k) { return gld(Src + (c0 + k) * ld + r0 + 32 * wr + 16 * q + li); },
-        [&](int q, int k) { return gld(UL + k * kPb + 32 * wc + 16 * q + li); }, lk);
+    bj_products<false, CPLX, RT, CT>(
+        p1, p2, p3, [&](int q, int k) { return gld(Src + (c0 + k) * ld + r0 + wr + 16 * q + li); },
+        [&](int q, int k) { return gld(UL + k * kPb + wc + 16 * q + li); }, lk);
     to_lds();
   }
   __syncthreads();
   if (!skK) {  // R = U_K^H T
-    bj_quarter<true>(
-        p1, p2, p3, [&](int q, int k) { return gld(UK + k * kPb + 32 * wr + 16 * q + li); },
-        [&](int q, int k) { return Ts[(32 * wc + 16 * q + li) * kPL + k]; }, lk);
+    bj_products<true, CPLX, RT, CT>(
+        p1, p2, p3, [&](int q, int k) { return gld(UK + k * kPb + wr + 16 * q + li); },
+        [&](int q, int k) {
+          const c128* v = Ts + (wc + 16 * q + li) * kPL + k;
+          return mk(v->x, v->y);
+        },
+        lk);
     __syncthreads();  // every wave has read T
     to_lds();
     __syncthreads();
   }
   // write out: rows of an A tile move with their blocks, V rows stay; an
   // off-diagonal A tile also gives its conjugate transpose
-  for (int e = t; e < kPb * kPb; e += blockDim.x) {
-    const int j = e / kPb, i = e % kPb;
+  for (int e = t; e < kPb * NCOL; e += 256) {
+    const int j = e / kPb, i = e % kPb, jt = j0 + j;
     const int64_t gr = isA ? (int64_t)bj_next(2 * K + i / kBs, h) * kBs + i % kBs : r0 + i;
-    const int64_t gc = (int64_t)bj_next(2 * L + j / kBs, h) * kBs + j % kBs;
+    const int64_t gc = (int64_t)bj_next(2 * L + jt / kBs, h) * kBs + jt % kBs;
     gst(Dst + gc * ld + gr, Ts[j * kPL + i]);
   }
   if (isA && K != L) {
-    for (int e = t; e < kPb * kPb; e += blockDim.x) {
-      const int i = e / kPb, j = e % kPb;  // conj(R(i, j)) goes to (row of j, column of i)
-      const int64_t gr = (int64_t)bj_next(2 * L + j / kBs, h) * kBs + j % kBs;
+    for (int e = t; e < kPb * NCOL; e += 256) {
+      const int i = e / NCOL, j = e % NCOL, jt = j0 + j;  // conj(R(i, jt)) to (row of jt, column of i)
+      const int64_t gr = (int64_t)bj_next(2 * L + jt / kBs, h) * kBs + jt % kBs;
       const int64_t gc = (int64_t)bj_next(2 * K + i / kBs, h) * kBs + i % kBs;
       gst(Dst + gc * ld + gr, cconj(Ts[j * kPL + i]));
     }
   }
+}
+
+template <int CS>
+__global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv, int cur) {
+  extern __shared__ __align__(16) char lds_raw[];
+  c128* Ts = reinterpret_cast<c128*>(lds_raw);  // 64 x (64 / CS), column-major, ld kPL
+  const BJDev d = dv[blockIdx.y];
+  const int wg = blockIdx.x / CS, part = blockIdx.x % CS;
+  if (wg >= d.h * (d.h + 1) / 2 + d.h * (d.mp / kPb)) return;
+  if (d.cplx)
+    bj_update_part<true, CS>(d, cur, Ts, wg, part);
+  else
+    bj_update_part<false, CS>(d, cur, Ts, wg, part);
 }
 
 // -------------------------------------------------------------- results
@@ -583,7 +611,7 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
     d.m = jobs[q].m;
     d.h = bj_h(d.m);
     d.mp = kPb * d.h;
-    d.pad = 0;
+    d.cplx = 0;  // set by k_bj_init
     auto take = [&](size_t bytes) {
       char* p = work + off;
       off += (bytes + 255) & ~(size_t)255;
@@ -607,8 +635,8 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)k_bj_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds_pairs);
-    (void)hipFuncSetAttribute((const void*)k_bj_update, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds_upd);
+    (void)hipFuncSetAttribute((const void*)k_bj_update<1>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_upd);
     (void)hipGetLastError();
     attr = true;
   }
@@ -624,6 +652,9 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   constexpr int kCUs = 256;
   const int rlog = 4 * max_h * nj <= kCUs ? 4 : 2 * max_h * nj <= kCUs ? 5 : 6;
   const int upd_wgs = max_h * (max_h + 1) / 2 + max_h * (max_mp / kPb);
+  // and tiles are split until there are four workgroups per CU
+  const int64_t tiles = (int64_t)upd_wgs * nj;
+  const int csplit = 4 * tiles <= 4 * kCUs ? 4 : 2 * tiles <= 4 * kCUs ? 2 : 1;
   for (int sw = 0; sw <= max_sweeps; ++sw) {
     k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd, cur);
     FB_HIP(hipGetLastError());
@@ -641,7 +672,12 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
     for (int r = 0; r < max_rounds; ++r) {
       k_bj_pairs<<<dim3(max_h << (6 - rlog), nj), kPairThreads, lds_pairs, st>>>(dvd, cur, rlog);
       FB_HIP(hipGetLastError());
-      k_bj_update<<<dim3(upd_wgs, nj), 256, lds_upd, st>>>(dvd, cur);
+      if (csplit == 4)
+        k_bj_update<4><<<dim3(4 * upd_wgs, nj), 256, lds_upd / 4, st>>>(dvd, cur);
+      else if (csplit == 2)
+        k_bj_update<2><<<dim3(2 * upd_wgs, nj), 256, lds_upd / 2, st>>>(dvd, cur);
+      else
+        k_bj_update<1><<<dim3(upd_wgs, nj), 256, lds_upd, st>>>(dvd, cur);
       FB_HIP(hipGetLastError());
       cur ^= 1;
     }

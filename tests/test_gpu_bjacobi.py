@@ -44,12 +44,13 @@ def test_pairs_real_and_complex(kind, m):
     assert np.abs(X.conj().T @ X - np.eye(m)).max() < 1e-12
 
 
-@pytest.mark.parametrize("blocks", [1, 20, 30])
+@pytest.mark.parametrize("blocks", [1, 10, 20, 30])
 @pytest.mark.parametrize("cplx", [True, False])
 def test_shared_out_pairs(cplx, blocks):
     """A call with few pairs shares each pair's transformation out over 4 or 2
-    workgroups, one with many does not: calls of 1, 20 and 30 equal blocks (5,
-    100 and 150 pairs), whose results are also equal to each other within a
+    workgroups and each tile of the update over 4 or 2, one with many does not:
+    calls of 1, 10, 20 and 30 equal blocks (5, 50, 100 and 150 pairs; 40 tiles
+    each), whose results are also equal to each other within a
     call.  (Between calls they differ by rounding: the Gram matrices' sums are
     split by the number of blocks.)"""
     import paper_2012_00506_amd as fb

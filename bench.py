@@ -69,7 +69,7 @@ def parse():
 
 # Sources of the block-solve and residual kernels: HBM byte counts recorded under profiles/
 # are reported as roofline traffic only while these files are unchanged.
-SOLVE_SOURCES = ["solve_kernel.h", "solve_f32.hip", "solve_f64.hip", "solve.hip", "solve_job.h",
+SOLVE_SOURCES = ["solve_kernel.h", "mfma.h", "solve_f32.hip", "solve_f64.hip", "solve.hip", "solve_job.h",
                  "fb_internal.h"]
 
 

@@ -589,6 +589,200 @@ __global__ void k_bj_vectors(const JacobiJob* __restrict__ jobs, BJDev* __restri
   }
 }
 
+// -------------------------------------------------------------- medium sizes
+// The cyclic Jacobi of k_jacobi, the same rotations and arithmetic, with a
+// launch per round: a workgroup takes 16 x 16 of the round's 2 x 2 blocks, or
+// 16 pairs of 64 rows of V, and forms the rotations of its own pairs from the
+// last round's matrix.  Rounds go from A to W and back (W is written last).
+// What bounds it: the launches' latency, about 5 us per round, where one
+// workgroup moved A and V through one CU.  A Rayleigh-Ritz step with m = 128
+// 15.8 -> 6.4 ms, m = 250 99 -> 12.8 ms, eight of m = 200 54 -> 16 ms.
+// JacobiJob.pad_: 2 * sweeps made, + 1 when converged.
+static constexpr int kJrPairs = 16;   // pairs of a workgroup's tile
+static constexpr int kJrRows = 64;    // rows of V per workgroup
+
+__device__ __forceinline__ int jr_player(int pos, int r, int mp) {
+  int v = pos + r;
+  v = v >= mp ? v - (mp - 1) : v;
+  return pos == 0 ? 0 : v;
+}
+
+__global__ void __launch_bounds__(1024) k_jr_norms(JacobiJob* __restrict__ jobs, int sweep,
+                                                   double tol) {
+  __shared__ double red[2][1024];
+  const JacobiJob jb = jobs[blockIdx.x];
+  const int m = jb.m, t = threadIdx.x;
+  if (m <= 0 || (jb.pad_ & 1)) return;
+  const int mp = m + (m & 1);
+  const bool odd = (sweep * (mp - 1)) & 1;
+  const c128* A = odd ? jb.W : jb.A;
+  const int64_t lda = odd ? jb.ldw : jb.lda;
+  if (sweep == 0)
+    for (int64_t e = t; e < (int64_t)m * m; e += 1024) {
+      const int j = (int)(e / m), i = (int)(e - (int64_t)j * m);
+      gst(jb.V + (int64_t)j * jb.ldv + i, mk(i == j ? 1.0 : 0.0, 0.0));
+    }
+  double f = 0.0, o = 0.0;
+  for (int64_t e = t; e < (int64_t)m * m; e += 1024) {
+    const int j = (int)(e / m), i = (int)(e - (int64_t)j * m);
+    const double a = cabs2(gld(A + (int64_t)j * lda + i));
+    f += a;
+    if (i != j) o += a;
+  }
+  red[0][t] = f;
+  red[1][t] = o;
+  __syncthreads();
+  for (int s = 512; s > 0; s >>= 1) {
+    if (t < s) {
+      red[0][t] += red[0][t + s];
+      red[1][t] += red[1][t + s];
+    }
+    __syncthreads();
+  }
+  if (t == 0) {
+    const bool done = red[1][0] <= tol * tol * red[0][0] || m == 1;
+    jobs[blockIdx.x].pad_ = done ? 2 * sweep + 1 : 2 * (sweep + 1);
+  }
+}
+
+__global__ void __launch_bounds__(256) k_jr_round(const JacobiJob* __restrict__ jobs, int sweep,
+                                                  int r) {
+  __shared__ BJRot rot[2 * kJrPairs];
+  __shared__ int2 pq[2 * kJrPairs];
+  const JacobiJob jb = jobs[blockIdx.y];
+  const int m = jb.m, mp = m + (m & 1), np = mp / 2;
+  if (m <= 0 || (jb.pad_ & 1) || r >= mp - 1) return;
+  const int nt = (np + kJrPairs - 1) / kJrPairs;
+  const int wg = blockIdx.x;
+  const bool isA = wg < nt * nt;
+  const int x = isA ? wg % nt : (wg - nt * nt) % nt, y = isA ? wg / nt : (wg - nt * nt) / nt;
+  if (!isA && y * kJrRows >= m) return;
+  const bool odd = (sweep * (mp - 1) + r) & 1;
+  const c128* A = odd ? jb.W : jb.A;
+  c128* An = odd ? jb.A : jb.W;
+  const int64_t lda = odd ? jb.ldw : jb.lda, ldn = odd ? jb.lda : jb.ldw;
+  const int t = threadIdx.x;
+  if (t < 2 * kJrPairs) {
+    // pairs of x (the rows' or V's), then of y
+    const int k = (t < kJrPairs ? x : y) * kJrPairs + t % kJrPairs;
+    BJRot o;
+    o.cs = 1.0;
+    o.sn = 0.0;
+    o.e = mk(1.0, 0.0);
+    int p = m, q = m;
+    if (k < np && (isA || t < kJrPairs)) {
+      const int a = jr_player(k, r, mp), b = jr_player(mp - 1 - k, r, mp);
+      p = min(a, b);
+      q = max(a, b);
+      if (q < m) {
+        const c128 c = gld(A + (int64_t)q * lda + p);
+        const double ac = sqrt(cabs2(c));
+        if (ac > 1e-300) {
+          const double app = gld(&A[(int64_t)p * lda + p].x), aqq = gld(&A[(int64_t)q * lda + q].x);
+          const double tau = (aqq - app) / (2.0 * ac);
+          const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + hypot(1.0, tau));
+          o.cs = 1.0 / sqrt(1.0 + tt * tt);
+          o.sn = tt * o.cs;
+          o.e = mk(c.x / ac, -c.y / ac);
+        }
+      }
+    }
+    rot[t] = o;
+    pq[t] = make_int2(p, q);
+  }
+  __syncthreads();
+  using X = BJElem<true>;
+  if (isA) {
+    const int kk = t % kJrPairs, ll = kJrPairs + t / kJrPairs;
+    const int pk = pq[kk].x, qk = pq[kk].y, pl = pq[ll].x, ql = pq[ll].y;
+    if (pk >= m || pl >= m) return;  // beyond the last pair
+    const bool qkv = qk < m, qlv = ql < m;
+    // a dummy player's elements are zero: read in place of them, then cleared
+    const int qks = qkv ? qk : pk, qls = qlv ? ql : pl;
+    const c128 a00 = gld(A + (int64_t)pl * lda + pk);
+    c128 a10 = gld(A + (int64_t)pl * lda + qks);
+    c128 a01 = gld(A + (int64_t)qls * lda + pk);
+    c128 a11 = gld(A + (int64_t)qls * lda + qks);
+    a10 = mk(qkv ? a10.x : 0.0, qkv ? a10.y : 0.0);
+    a01 = mk(qlv ? a01.x : 0.0, qlv ? a01.y : 0.0);
+    a11 = mk(qkv && qlv ? a11.x : 0.0, qkv && qlv ? a11.y : 0.0);
+    const BJRot rk = rot[kk], rl = rot[ll];
+    a01 = X::mul(rl.e, a01);
+    a11 = X::mul(rl.e, a11);
+    const c128 b00 = X::minus(rl.cs, a00, rl.sn, a01), b01 = X::plus(rl.sn, a00, rl.cs, a01);
+    const c128 b10 = X::mulc(rk.e, X::minus(rl.cs, a10, rl.sn, a11));
+    const c128 b11 = X::mulc(rk.e, X::plus(rl.sn, a10, rl.cs, a11));
+    gst(An + (int64_t)pl * ldn + pk, X::minus(rk.cs, b00, rk.sn, b10));
+    if (qkv) gst(An + (int64_t)pl * ldn + qk, X::plus(rk.sn, b00, rk.cs, b10));
+    if (qlv) gst(An + (int64_t)ql * ldn + pk, X::minus(rk.cs, b01, rk.sn, b11));
+    if (qkv && qlv) gst(An + (int64_t)ql * ldn + qk, X::plus(rk.sn, b01, rk.cs, b11));
+  } else {
+#pragma unroll
+    for (int g = 0; g < kJrPairs * kJrRows / 256; ++g) {
+      const int k = t / kJrRows + g * (256 / kJrRows), i = y * kJrRows + t % kJrRows;
+      const int p = pq[k].x, q = pq[k].y;
+      if (q >= m || i >= m) continue;
+      const BJRot o = rot[k];
+      const c128 vp = gld(jb.V + (int64_t)p * jb.ldv + i);
+      const c128 vq = X::mulu(o.e, gld(jb.V + (int64_t)q * jb.ldv + i));
+      gst(jb.V + (int64_t)p * jb.ldv + i, X::minus(o.cs, vp, o.sn, vq));
+      gst(jb.V + (int64_t)q * jb.ldv + i, X::plus(o.sn, vp, o.cs, vq));
+    }
+  }
+}
+
+// eigenvalues ascending (rank by value, ties by index), vectors follow
+__global__ void __launch_bounds__(1024) k_jr_final(const JacobiJob* __restrict__ jobs) {
+  __shared__ double d[kSmallJacobi];
+  const JacobiJob jb = jobs[blockIdx.x];
+  const int m = jb.m, mp = m + (m & 1), t = threadIdx.x, sweeps = jb.pad_ >> 1;
+  if (m <= 0) return;
+  const bool odd = (sweeps * (mp - 1)) & 1;
+  const c128* A = odd ? jb.W : jb.A;
+  const int64_t lda = odd ? jb.ldw : jb.lda;
+  for (int i = t; i < m; i += 1024) d[i] = gld(&A[(int64_t)i * lda + i].x);
+  __syncthreads();
+  for (int i = t; i < m; i += 1024) {
+    const double wi = d[i];
+    int rank = 0;
+    for (int j = 0; j < m; ++j) rank += (d[j] < wi || (d[j] == wi && j < i)) ? 1 : 0;
+    gst(jb.w + rank, wi);
+    gst(jb.order + rank, i);
+  }
+  if (t == 0 && jb.sweeps) gst(jb.sweeps, sweeps);
+  __syncthreads();
+  for (int64_t e = t; e < (int64_t)m * m; e += 1024) {
+    const int k = (int)(e / m), i = (int)(e - (int64_t)k * m);
+    gst(jb.W + (int64_t)k * jb.ldw + i, gld(jb.V + (int64_t)gld(jb.order + k) * jb.ldv + i));
+  }
+}
+
+static int round_jacobi(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, int max_sweeps,
+                        double tol, hipStream_t st) {
+  const int nj = (int)jobs.size();
+  int maxm = 0;
+  for (const JacobiJob& j : jobs) maxm = std::max(maxm, j.m);
+  const int mp = maxm + (maxm & 1), nt = (mp / 2 + kJrPairs - 1) / kJrPairs;
+  const int wgs = nt * nt + nt * ((maxm + kJrRows - 1) / kJrRows);
+  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+    k_jr_norms<<<nj, 1024, 0, st>>>(jobs_dev, sweep, tol);
+    FB_HIP(hipGetLastError());
+    FB_HIP(hipMemcpyAsync(jobs.data(), jobs_dev, sizeof(JacobiJob) * nj, hipMemcpyDeviceToHost, st));
+    FB_HIP(hipStreamSynchronize(st));
+    int rounds = 0;
+    for (const JacobiJob& j : jobs)
+      if (j.m > 0 && !(j.pad_ & 1)) rounds = std::max(rounds, j.m + (j.m & 1) - 1);
+    if (rounds == 0) break;
+    for (int r = 0; r < rounds; ++r) {
+      k_jr_round<<<dim3(wgs, nj), 256, 0, st>>>(jobs_dev, sweep, r);
+      FB_HIP(hipGetLastError());
+    }
+  }
+  k_jr_final<<<nj, 1024, 0, st>>>(jobs_dev);
+  FB_HIP(hipGetLastError());
+  return 0;
+}
+
 // -------------------------------------------------------------- driver
 static int bj_h(int m) { return (m + kPb - 1) / kPb; }
 
@@ -728,7 +922,16 @@ int reduced_eig(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, const EigWork&
   if (all.empty()) return 0;
   FB_HIP(hipMemcpyAsync(jobs_dev, all.data(), sizeof(JacobiJob) * all.size(),
                         hipMemcpyHostToDevice, st));
-  if (!small.empty()) FB_TRY(launch_jacobi((int)small.size(), jobs_dev, max_sweeps, tol, st));
+  if (!small.empty()) {
+    int maxm = 0;
+    for (const JacobiJob& j : small) maxm = std::max(maxm, j.m);
+    if (maxm >= kRoundJacobi) {
+      ProfScope ps(FB_PROF_JACOBI, st, 0.0);
+      FB_TRY(round_jacobi(small, jobs_dev, max_sweeps, tol, st));
+    } else {
+      FB_TRY(launch_jacobi((int)small.size(), jobs_dev, max_sweeps, tol, st));
+    }
+  }
   if (!large.empty()) {
     if (!w.bj) return FB_ERR_INTERNAL;
     ProfScope ps(FB_PROF_JACOBI, st, 0.0);

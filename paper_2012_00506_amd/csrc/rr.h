@@ -60,9 +60,13 @@ size_t block_jacobi_bytes(int m);
 int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, char* work,
                  void* dv_dev, double* norms_dev, int max_sweeps, double tol, hipStream_t st);
 
-// Hermitian eigensolver dispatch: matrices up to kSmallJacobi on one
-// workgroup each, larger ones by block Jacobi.
+// Hermitian eigensolver dispatch: matrices up to kSmallJacobi by the cyclic
+// Jacobi, larger ones by block Jacobi.  The cyclic Jacobi runs on one
+// workgroup per matrix, or, in a call with one of kRoundJacobi columns or
+// more, with a launch per round over the whole chip: the same bits, one
+// matrix of 64 columns 3.0 ms against 2.9, of 97 5.0 against 6.9.
 constexpr int kSmallJacobi = 256;
+constexpr int kRoundJacobi = 80;
 struct EigWork {
   char* bj = nullptr;       // block Jacobi buffers
   void* dv = nullptr;       // descriptors

@@ -1,4 +1,6 @@
-"""The pair problems of the parallel block Jacobi, real and complex: a reduced
+"""The Jacobi solvers of the reduced matrices around their limits (one
+workgroup below 80 columns, a launch per round up to 256, blocks above), and
+the pair problems of the parallel block Jacobi, real and complex: a reduced
 matrix whose pairs are all real, all complex, or some of each (a basis on two
 decoupled halves of the matrix, the first one real).  Oracle: LAPACK's
 eigenvalues of the same reduced matrix.  Tolerance: two-sided Jacobi and LAPACK
@@ -15,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["real", "complex", "mixed"])
-@pytest.mark.parametrize("m", [257, 320, 385])
+@pytest.mark.parametrize("m", [79, 80, 81, 113, 255, 256, 257, 320, 385])
 def test_pairs_real_and_complex(kind, m):
     import paper_2012_00506_amd as fb
     n, b, h = 900, 6, 450

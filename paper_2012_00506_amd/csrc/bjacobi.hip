@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(kPairThreads) k_bj_pairs(BJDev* __restrict__ d
 // What bounds it: the latency of the two dependent products of an A tile, at
 // the few tiles that a call has for 256 CUs.  Whole tiles took 35 us per launch
 // for two complex matrices of 640 columns and 28 us for a real one of 320; now
-// 26 (CS = 2) and 12 us (CS = 4).
+// 20 (CS = 2) and 11 us (CS = 4); sixteen of 1500, whole tiles, 740 -> 620 us.
 template <bool CONJA, bool CPLX, int RT, int CT, typename FA, typename FB>
 __device__ __forceinline__ void bj_products(bd4 (&p1)[RT][CT], bd4 (&p2)[RT][CT],
                                             bd4 (&p3)[RT][CT], FA fa, FB fb, int lk) {
@@ -452,11 +452,11 @@ __device__ __forceinline__ void bj_products(bd4 (&p1)[RT][CT], bd4 (&p2)[RT][CT]
 }
 
 template <bool CPLX, int CS>
-__device__ __forceinline__ void bj_update_part(const BJDev& d, int cur, c128* Ts, int wg,
-                                               int part) {
+__device__ __forceinline__ void bj_update_part(const c128* As, c128* Ad, const c128* Vs, c128* Vd,
+                                               const c128* U, const int32_t* skip, int mp, int h,
+                                               c128* Ts, int wg, int part) {
   constexpr int RT = CS == 1 ? 2 : 1, CT = CS == 4 ? 1 : 2;
   constexpr int NCOL = kPb / CS;
-  const int h = d.h;
   const int nA = h * (h + 1) / 2;
   const bool isA = wg < nA;
   int K, L;
@@ -472,19 +472,18 @@ __device__ __forceinline__ void bj_update_part(const BJDev& d, int cur, c128* Ts
     K = (wg - nA) / h;  // row tile of V
     L = (wg - nA) % h;
   }
-  // (selects, not indexing: an indexed member array would live in scratch)
-  const c128* Src = isA ? (cur ? d.A[1] : d.A[0]) : (cur ? d.V[1] : d.V[0]);
-  c128* Dst = isA ? (cur ? d.A[0] : d.A[1]) : (cur ? d.V[0] : d.V[1]);
-  const int64_t ld = d.mp;
+  const c128* Src = isA ? As : Vs;
+  c128* Dst = isA ? Ad : Vd;
+  const int64_t ld = mp;
   const int64_t r0 = (int64_t)K * kPb, c0 = (int64_t)L * kPb;
-  const int skK = isA ? gld(d.skip + K) : 1, skL = gld(d.skip + L);
+  const int skK = isA ? gld(skip + K) : 1, skL = gld(skip + L);
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int j0 = NCOL * part;  // the workgroup's columns of the tile
   // the wave's rows and, within those columns, columns
   const int wr = 16 * RT * (CS == 1 ? w & 1 : w), wc = CS == 1 ? 32 * (w >> 1) : 0;
   const int li = lane & 15, lk = lane >> 4;
-  const c128* UL = d.U + (size_t)L * kPb * kPb + j0;
-  const c128* UK = d.U + (size_t)K * kPb * kPb;
+  const c128* UL = U + (size_t)L * kPb * kPb + j0;
+  const c128* UK = U + (size_t)K * kPb * kPb;
   bd4 p1[RT][CT], p2[RT][CT], p3[RT][CT];
   auto to_lds = [&]() {
 #pragma unroll
@@ -542,16 +541,21 @@ __device__ __forceinline__ void bj_update_part(const BJDev& d, int cur, c128* Ts
 }
 
 template <int CS>
-__global__ void __launch_bounds__(256) k_bj_update(BJDev* __restrict__ dv, int cur) {
+__global__ void __launch_bounds__(256, 2) k_bj_update(BJDev* __restrict__ dv, int cur) {
   extern __shared__ __align__(16) char lds_raw[];
   c128* Ts = reinterpret_cast<c128*>(lds_raw);  // 64 x (64 / CS), column-major, ld kPL
-  const BJDev d = dv[blockIdx.y];
+  const BJDev* d = dv + blockIdx.y;
   const int wg = blockIdx.x / CS, part = blockIdx.x % CS;
-  if (wg >= d.h * (d.h + 1) / 2 + d.h * (d.mp / kPb)) return;
-  if (d.cplx)
-    bj_update_part<true, CS>(d, cur, Ts, wg, part);
+  const int h = d->h, mp = d->mp;
+  if (wg >= h * (h + 1) / 2 + h * (mp / kPb)) return;
+  // (by constant members: an indexed member array would live in scratch)
+  c128 *A0 = d->A[0], *A1 = d->A[1], *V0 = d->V[0], *V1 = d->V[1];
+  const c128 *As = cur ? A1 : A0, *Vs = cur ? V1 : V0;
+  c128 *Ad = cur ? A0 : A1, *Vd = cur ? V0 : V1;
+  if (d->cplx)
+    bj_update_part<true, CS>(As, Ad, Vs, Vd, d->U, d->skip, mp, h, Ts, wg, part);
   else
-    bj_update_part<false, CS>(d, cur, Ts, wg, part);
+    bj_update_part<false, CS>(As, Ad, Vs, Vd, d->U, d->skip, mp, h, Ts, wg, part);
 }
 
 // -------------------------------------------------------------- results

@@ -278,8 +278,9 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
 
   int neg = 0, zero = 0, par = 0;
   // whole blocks: the columns past the last are the identity's, whose pivots
-  // count as positive
+  // are positive, or tiny where pivmin is above 1
   const int nblk = (int)((ncols + 15) / 16);
+  if (pivmin > 1.0) zero -= (int)(16 * (int64_t)nblk - ncols);
   constexpr int NPF = T;  // (16 (T - 1) + 1) 16 entries over 256 threads
   E pf[NPF];
   const c128* pfp[NPF];  // this thread's entries of the next block row to enter
@@ -296,19 +297,20 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
     // entering block row, fetched over the block's four panels
     const bool last = a.mode != kHalves && blk + 1 == nblk;
     const int64_t X16 = 16 * ((int64_t)blk + T);
+    int inside = 16;  // of its rows
     if (!last) {
       if (X16 + 16 <= n) {
 #pragma unroll
         for (int q = 0; q < NPF; ++q) pf[q] = Ld::load(pfp[q]);
       } else {
-        // rows past the last: the identity's (zeros with diagonal 1 + sigma,
-        // as sigma is taken off below)
+        // rows past the last: the identity's
+        inside = X16 < n ? (int)n & 15 : 0;
 #pragma unroll
         for (int q = 0; q < NPF; ++q) {
           const int e = t + q * kInertiaThreads;
           const bool in = X16 + (e & 15) < n;
           pf[q] = Ld::load(in ? pfp[q] : Bd);
-          if (!in) pf[q] = Ld::real(e < 16 ? 1.0 + sigma : 0.0);
+          if (!in) pf[q] = Ld::real(e < 16 ? 1.0 : 0.0);
         }
       }
 #pragma unroll
@@ -383,7 +385,7 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
             asm volatile("" : "+v"(x.x), "+v"(x.y));
           else
             asm volatile("" : "+v"(x));
-          if (q == 0 && t < 16) x = Ld::real(re_of(x) - sigma);
+          if (q == 0 && t < inside) x = Ld::real(re_of(x) - sigma);
           lput(Wl + pfl[q], x);
         }
       }

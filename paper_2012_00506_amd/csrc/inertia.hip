@@ -29,9 +29,11 @@
 // leading rows downwards, another the trailing rows upwards (the same code on
 // the reversed, conjugated band), and a third launch adds the two Schur
 // complements on the 16-aligned separator between them and finishes it.
-// Every elimination order gives the same inertia as long as no pivot is
-// zero; a shift that meets one is redone in the plain order, whose treatment
-// of zero pivots is the documented one.
+// In exact arithmetic every elimination order gives the same inertia as long
+// as no pivot is zero, but without pivoting the digits that an order keeps
+// depend on its smallest pivots.  A shift that meets a zero pivot, or one below
+// sqrt(eps) ||B||_1 on the way up or in the separator, is redone in the plain
+// order, leading rows first, whose counts are the documented ones.
 #include <type_traits>
 
 #include "fb_internal.h"
@@ -141,7 +143,7 @@ struct InertiaArgs {
   const double* stats;
   int32_t* counts;  // 3 per shift
   int mode;
-  int gated;        // kFull: only shifts whose counts hold a zero pivot
+  int gated;        // kFull: only shifts whose counts hold a zero or small pivot
   int h0, h1;       // blocks of 16 rows eliminated from the top and the bottom
   int32_t* part;    // 4 per shift: (neg, zero) of the two halves
   c128* dump;       // 2 per shift: the window left by a half, tile by tile
@@ -196,7 +198,10 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
   const c128* Bd = a.Bd;
   const double sigma = a.shifts[s];
   const double eps = 2.220446049250313e-16;
-  const double pivmin = eps * eps * a.stats[0];
+  // the orders that only the split has: a pivot below sqrt(eps) ||B||_1 lets
+  // the elements grow until half their digits are lost, and is reported as a
+  // zero one, for which the plain order is taken
+  const double pivmin = (half || a.mode == kMiddle ? 0x1p-26 : eps * eps) * a.stats[0];
   // rows of this elimination and of them the ones it eliminates
   const int64_t sep0 = (int64_t)16 * a.h0;                       // first separator row
   const int64_t S = n - (int64_t)16 * (a.h0 + a.h1);             // separator rows

@@ -558,14 +558,15 @@ void carve_feast(Arena& ar, const Band& bd, int W, int maxm, int ne, bool ir, in
   fb.perm_dev = ar.take<int32_t>(maxm);
   fb.acc_dev = ar.take<AccJob>(W);
   fb.tile = solve_tile<R>(bd.b, (size_t)W * ((maxm + 31) / 32) * P);
-  const int max_jobs = W * ((maxm + fb.tile - 1) / fb.tile);
+  RefineSize rsize;
+  rsize.add(refine_size(bd.b, maxm), W * P);
   fb.P = P;
   fb.Xp.assign((size_t)W * P, nullptr);
   for (int a = 0; a < W; ++a) {
     fb.Xp[(size_t)a * P] = fb.sb[a].X;
     for (int p = 1; p < P; ++p) fb.Xp[(size_t)a * P + p] = ar.take<c128>((size_t)n * m);
   }
-  carve_refine(ar, bd, fb.tile, max_jobs * P, ir, ir, fb.rb);
+  carve_refine(ar, bd, fb.tile, rsize, ir, ir, fb.rb);
 }
 
 // Orthonormalisation and Rayleigh-Ritz of the filtered blocks of the slots
@@ -1079,20 +1080,21 @@ int filter_impl(const fb_band* B, int nslice, const double* lo, const double* hi
   size_t tiles32 = 0;
   for (int i = 0; i < nslice; ++i) tiles32 += (size_t)((m[i] + 31) / 32) * npair;
   const int tile = solve_tile<R>(bd.b, tiles32);
-  int max_jobs = 0;
+  RefineSize one, rsize;  // of one (node, direction) pair and of a launch
   size_t cols = 0;
   for (int i = 0; i < nslice; ++i) {
-    max_jobs += (m[i] + tile - 1) / tile;
+    one.add(refine_size(bd.b, m[i]), 1);
     cols += std::max(m[i], 1);
   }
   const int P = pairs_per_launch(o->hbm_budget, o->pairs, o->batched != 0, npair,
-                                 ar.used + refine_bytes(bd, tile, max_jobs, ir, need_res),
+                                 ar.used + refine_bytes(bd, one, ir, need_res),
                                  (size_t)n * cols * sizeof(c128));
   std::vector<c128*> Xp((size_t)nslice * P);
   for (int i = 0; i < nslice; ++i)
     for (int p = 0; p < P; ++p) Xp[(size_t)i * P + p] = ar.take<c128>((size_t)n * std::max(m[i], 1));
   RefineBufs rb;
-  carve_refine(ar, bd, tile, max_jobs * P, ir, need_res, rb);
+  rsize.add(one, P);
+  carve_refine(ar, bd, tile, rsize, ir, need_res, rb);
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;
@@ -1135,9 +1137,9 @@ int filter_impl(const fb_band* B, int nslice, const double* lo, const double* hi
     if (!aj.empty())
       FB_HIP(hipMemcpyAsync(acc_dev, aj.data(), sizeof(AccJob) * aj.size(), hipMemcpyHostToDevice, st));
     char key[512];
-    snprintf(key, sizeof key, "%d|%p|%lld|%d|%d|%lld|%d|%d|%d|%d|%.17g|%d|%d|%p|%zu|%p",
+    snprintf(key, sizeof key, "%d|%p|%lld|%d|%d|%lld|%d|%d|%d|%d|%.17g|%d|%d|%d|%p|%zu|%p",
              (int)sizeof(R), B->ab, (long long)n, B->b, B->dtype, (long long)B->ldab, nslice, ne,
-             o->precision, o->ir_max, o->ir_tol, P, (int)need_res, work, *lwork, (void*)st);
+             o->precision, o->ir_max, o->ir_tol, P, (int)need_res, tile, work, *lwork, (void*)st);
     std::string k(key);
     for (int i = 0; i < nslice; ++i) {
       snprintf(key, sizeof key, "|%d:%p:%lld:%p:%lld", m[i], Y[i], (long long)ldy[i], Q[i],

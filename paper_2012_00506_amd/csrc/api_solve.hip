@@ -165,30 +165,36 @@ size_t ir_wave_jobs(int64_t n, int tile) {
   return std::max<size_t>(w, 64);
 }
 
-void carve_refine(Arena& ar, const Band& bd, int tile, int max_jobs, bool ir, bool need_res,
+RefineSize refine_size(int b, int m) {
+  const int gc = residual_cols(block_size(b));
+  return {(m + 15) / 16, (m + gc - 1) / gc};
+}
+
+void carve_refine(Arena& ar, const Band& bd, int tile, RefineSize size, bool ir, bool need_res,
                   RefineBufs& rb) {
   rb.tile = tile;
   rb.gcols = residual_cols(block_size(bd.b));  // >= tile (variant_fits)
-  rb.cap_jobs = std::max(max_jobs, 1);
+  rb.cap_jobs = std::max(size.jobs, 1);
+  rb.cap_groups = std::max(size.groups, 1);
   rb.jobs_dev = ar.take<SolveJob>(rb.cap_jobs);
   // the buffer is sized in complex128 columns (callers' slice and pair counts
   // follow from its size) and holds complex64 residuals: twice the groups
-  const size_t blocks = std::min<size_t>(ir_wave_jobs(bd.n, rb.gcols), (size_t)rb.cap_jobs);
-  rb.wave = need_res ? std::min<size_t>(2 * blocks, (size_t)rb.cap_jobs) : 0;
+  const size_t blocks = std::min<size_t>(ir_wave_jobs(bd.n, rb.gcols), (size_t)rb.cap_groups);
+  rb.wave = need_res ? std::min<size_t>(2 * blocks, (size_t)rb.cap_groups) : 0;
   // every group has a residual job; a group's corrections are its tiles
-  rb.rjobs_dev = need_res ? ar.take<ResJob>(rb.cap_jobs) : nullptr;
+  rb.rjobs_dev = need_res ? ar.take<ResJob>(rb.cap_groups) : nullptr;
   rb.cjobs_dev = ir ? ar.take<SolveJob>(rb.cap_jobs) : nullptr;
   rb.rbuf = need_res && ir ? ar.take<c64>(2 * blocks * (size_t)bd.n * rb.gcols) : nullptr;
   rb.part = need_res ? ar.take<double>(residual_part_doubles(bd.n, (int)rb.wave)) : nullptr;
-  rb.ratio = need_res ? ar.take<double>(rb.cap_jobs) : nullptr;
-  rb.flag = need_res ? ar.take<int32_t>(rb.cap_jobs) : nullptr;
-  rb.npass = need_res ? ar.take<int32_t>(rb.cap_jobs) : nullptr;
+  rb.ratio = need_res ? ar.take<double>(rb.cap_groups) : nullptr;
+  rb.flag = need_res ? ar.take<int32_t>(rb.cap_groups) : nullptr;
+  rb.npass = need_res ? ar.take<int32_t>(rb.cap_groups) : nullptr;
 }
 
-size_t refine_bytes(const Band& bd, int tile, int max_jobs, bool ir, bool need_res) {
+size_t refine_bytes(const Band& bd, RefineSize size, bool ir, bool need_res) {
   Arena q;
   RefineBufs rb;
-  carve_refine(q, bd, tile, max_jobs, ir, need_res, rb);
+  carve_refine(q, bd, 16, size, ir, need_res, rb);
   return q.used;
 }
 
@@ -238,6 +244,7 @@ int refine_prepare(const Band& bd, const std::vector<SolveJob>& jobs,
     groups.push_back({i, i});
   }
   const int ng = (int)groups.size();
+  if (ng > rb.cap_groups) return FB_ERR_INTERNAL;
   plan.ng = ng;
   // residual job of every group (its block in the wave's residual buffer)
   // and the correction jobs of every group, contiguous per wave
@@ -503,8 +510,12 @@ int shifted_solve_impl(const fb_band* B, int nsys, const double* z, const int32_
 
   // jobs: every (system, direction, tile)
   size_t tiles32 = 0;
-  for (int s = 0; s < nsys; ++s)
-    tiles32 += (size_t)((m[s] + 31) / 32) * ((X[s] != nullptr) + (XH && XH[s]));
+  RefineSize rsize;
+  for (int s = 0; s < nsys; ++s) {
+    const int dirs = (X[s] != nullptr) + (XH && XH[s]);
+    tiles32 += (size_t)((m[s] + 31) / 32) * dirs;
+    rsize.add(refine_size(bd.b, m[s]), dirs);
+  }
   const int tile = solve_tile<R>(bd.b, tiles32);
   std::vector<SolveJob> jobs;
   for (int s = 0; s < nsys; ++s)
@@ -528,7 +539,7 @@ int shifted_solve_impl(const fb_band* B, int nsys, const double* z, const int32_
     }
   const bool need_res = ir || resid != nullptr;
   RefineBufs rb;
-  carve_refine(ar, bd, tile, (int)jobs.size(), ir, need_res, rb);
+  carve_refine(ar, bd, tile, rsize, ir, need_res, rb);
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;

@@ -108,10 +108,10 @@ int factor_check(int nsys, FactorBufs<R>& f, hipStream_t st);
 struct RefineBufs {
   int tile = 32;
   int gcols = 32;  // columns per residual group
-  int cap_jobs = 0;
+  int cap_jobs = 0, cap_groups = 0;
   size_t wave = 0;           // groups whose residual blocks fit at once
   SolveJob* jobs_dev = nullptr;
-  ResJob* rjobs_dev = nullptr;   // one per group (cap_jobs)
+  ResJob* rjobs_dev = nullptr;   // one per group
   SolveJob* cjobs_dev = nullptr; // correction jobs of every group
   c64* rbuf = nullptr;           // residual blocks of one wave of groups (ir)
   double* part = nullptr;
@@ -119,7 +119,19 @@ struct RefineBufs {
   int32_t* flag = nullptr;       // per group
   int32_t* npass = nullptr;      // per group
 };
-void carve_refine(Arena& ar, const Band& bd, int tile, int max_jobs, bool ir, bool need_res,
+// Capacity of the refinement buffers: solve jobs of 16 columns, whatever the
+// tile width, and residual groups, so that a call's workspace grows with its
+// columns and does not depend on the width that is chosen or tuned.
+struct RefineSize {
+  int jobs = 0, groups = 0;
+  void add(RefineSize s, int times) {
+    jobs += s.jobs * times;
+    groups += s.groups * times;
+  }
+};
+// of one block of m columns in one direction
+RefineSize refine_size(int b, int m);
+void carve_refine(Arena& ar, const Band& bd, int tile, RefineSize size, bool ir, bool need_res,
                   RefineBufs& rb);
 
 // Complex128 fallback of the refined complex64 solves: a system whose FP64
@@ -145,7 +157,7 @@ struct C128Fallback {
 // quarter of a FEAST wave's systems, whose factors are kept between iterations
 inline int fallback_cap(int nsys) { return nsys < 2 ? nsys : 2; }
 inline int feast_fallback_cap(int nsys) { return std::min(nsys, std::max(2, nsys / 4)); }
-size_t refine_bytes(const Band& bd, int tile, int max_jobs, bool ir, bool need_res);
+size_t refine_bytes(const Band& bd, RefineSize size, bool ir, bool need_res);
 // Solve + refinement of one batch of jobs in three stages (solve_refine runs
 // all three): tables to the device, kernel launches (no host round-trip, so
 // they can be captured), read-back and complex128 fallback.

@@ -520,8 +520,6 @@ void carve_feast(Arena& ar, const Band& bd, int W, int maxm, int ne, bool ir, in
   }
   fb.shifts = ar.take<double>(2 * W);
   fb.cnt = ar.take<int32_t>(6 * W);
-  size_t iscr = inertia_scratch_bytes(bd, 2 * W);
-  fb.iscratch = iscr ? (void*)ar.take<char>(iscr) : nullptr;
   fb.sb.assign(W, SliceBufs{});
   const int m = maxm;
   for (int a = 0; a < W; ++a) {
@@ -567,6 +565,7 @@ void carve_feast(Arena& ar, const Band& bd, int W, int maxm, int ne, bool ir, in
     for (int p = 1; p < P; ++p) fb.Xp[(size_t)a * P + p] = ar.take<c128>((size_t)n * m);
   }
   carve_refine(ar, bd, fb.tile, rsize, ir, ir, fb.rb);
+  if (ne > 0) fb.iscratch = ar.take_optional(inertia_scratch_bytes(bd, 2 * W));
 }
 
 // Orthonormalisation and Rayleigh-Ritz of the filtered blocks of the slots

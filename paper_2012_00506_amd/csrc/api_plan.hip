@@ -114,11 +114,9 @@ extern "C" int slice_plan(const fb_band* B, const fb_plan_opts* o, double* bound
   const int cap = 2 * (K + 1) + K;
   double* sh = ar.take<double>(cap);
   int32_t* cnt = ar.take<int32_t>(3 * (size_t)cap);
-  size_t scb = inertia_scratch_bytes(bd, cap);
-  void* scratch = scb ? (void*)ar.take<char>(scb) : nullptr;
   const bool learned = o->mode == FB_PLAN_LEARNED;
   float *xin = nullptr, *yout = nullptr, *hid = nullptr;
-  Arena far;  // features scratch, carved after everything else
+  Arena far;  // features scratch
   if (learned && o->planner) {
     xin = ar.take<float>(kPlanFeatures);
     yout = ar.take<float>(kPlanOutputs);
@@ -131,6 +129,7 @@ extern "C" int slice_plan(const fb_band* B, const fb_plan_opts* o, double* bound
     far.cap = far.used + 256;
     far.used = 0;
   }
+  void* scratch = ar.take_optional(inertia_scratch_bytes(bd, cap));
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;
@@ -443,8 +442,7 @@ extern "C" int slice_plan_prev(const fb_band* B, const double* prev, int64_t npr
   const int cap = 2 * (K + 1);
   double* sh = ar.take<double>(cap);
   int32_t* cnt = ar.take<int32_t>(3 * (size_t)cap);
-  size_t scb = inertia_scratch_bytes(bd, cap);
-  void* scratch = scb ? (void*)ar.take<char>(scb) : nullptr;
+  void* scratch = ar.take_optional(inertia_scratch_bytes(bd, cap));
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;
@@ -539,8 +537,7 @@ extern "C" int slice_certify(const fb_band* B, int32_t nb, double* bounds, doubl
   const int cap = 2 * nb;
   double* sh = ar.take<double>(cap);
   int32_t* cnt = ar.take<int32_t>(3 * (size_t)cap);
-  size_t scb = inertia_scratch_bytes(bd, cap);
-  void* scratch = scb ? (void*)ar.take<char>(scb) : nullptr;
+  void* scratch = ar.take_optional(inertia_scratch_bytes(bd, cap));
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;

@@ -125,8 +125,7 @@ int inertia_call(const fb_band* B, int32_t nshift, const double* shifts, int32_t
   FB_TRY(ingest_band(B, bd, ar, st, false));
   double* sh = ar.take<double>(std::max(nshift, 1));
   int32_t* cnt = ar.take<int32_t>(3 * (size_t)std::max(nshift, 1));
-  size_t scb = split ? inertia_scratch_bytes(bd, nshift) : 0;
-  void* scratch = scb ? (void*)ar.take<char>(scb) : nullptr;
+  void* scratch = ar.take_optional(split ? inertia_scratch_bytes(bd, nshift) : 0);
   if (work == nullptr) {
     *lwork = ar.used;
     return 0;

@@ -133,6 +133,15 @@ struct Arena {
     if (base == nullptr) return nullptr;
     return reinterpret_cast<T*>(base + off);
   }
+  // Scratch that a call can do without, taken after everything else: counted
+  // in a query, null where the workspace ends before it.
+  char* take_optional(size_t bytes) {
+    const size_t before = used;
+    char* p = bytes ? take<char>(bytes) : nullptr;
+    if (base == nullptr || used <= cap) return p;
+    used = before;
+    return nullptr;
+  }
   bool fits() const { return base == nullptr || used <= cap; }
 };
 
@@ -171,8 +180,8 @@ constexpr int kFiniteParts = 64;
 int launch_inertia(const Band& bd, int nshift, const double* shifts_dev,
                    int32_t* cnt_dev, void* scratch, hipStream_t st);
 size_t inertia_scratch_bytes(const Band& bd, int nshift);
-// band_inertia; split = false takes no scratch beyond the band copy, the
-// shifts and the counts
+// band_inertia; a query with split = false leaves out the scratch of split
+// eliminations, without which shifts are eliminated whole
 int inertia_call(const fb_band* B, int32_t nshift, const double* shifts, int32_t* n_neg,
                  int32_t* n_zero, int32_t* n_pos, void* work, size_t* lwork, bool split,
                  void* stream);

@@ -46,20 +46,14 @@ extern "C" int band_inertia_noalloc(const fb_band* B, int32_t nshift, const doub
   if (nshift > 0 && !n_neg) return -4;
   for (int i = 0; i < nshift; ++i)
     if (!isfinite(shifts[i])) return -3;
-  // size of the work as band_inertia lays it out (a host-only query), with the
-  // scratch of split eliminations where that fits
+  // size of the work as band_inertia lays it out (a host-only query), without
+  // the scratch of split eliminations, which the call takes where it fits
   size_t need = 0;
-  bool split = true;
-  FB_TRY(fb::inertia_call(B, nshift, shifts, n_neg, n_zero, n_pos, nullptr, &need, split, stream));
-  if (need > (size_t)FB_NOALLOC_SCRATCH_BYTES) {
-    split = false;
-    FB_TRY(fb::inertia_call(B, nshift, shifts, n_neg, n_zero, n_pos, nullptr, &need, split,
-                            stream));
-  }
+  FB_TRY(fb::inertia_call(B, nshift, shifts, n_neg, n_zero, n_pos, nullptr, &need, false, stream));
   if (need > (size_t)FB_NOALLOC_SCRATCH_BYTES) return FB_ERR_TOO_LARGE;
   if (nshift == 0) return 0;
   void* p = nullptr;
   FB_TRY(scratch_ptr(&p));
   size_t cap = FB_NOALLOC_SCRATCH_BYTES;
-  return fb::inertia_call(B, nshift, shifts, n_neg, n_zero, n_pos, p, &cap, split, stream);
+  return band_inertia(B, nshift, shifts, n_neg, n_zero, n_pos, p, &cap, stream);
 }

@@ -917,6 +917,11 @@ void carve_eig_work(Arena& ar, const std::vector<int>& ms, EigWork& w) {
   w.norms = n ? ar.take<double>(2 * (size_t)n) : nullptr;
 }
 
+bool rounds_pay(int maxm, int64_t sum2, int cus) {
+  const int64_t room = 80 * (int64_t)maxm * maxm - 450000;  // of 256 CUs
+  return maxm >= kRoundJacobi && 256 * sum2 <= room * (cus > 0 ? cus : 256);
+}
+
 int reduced_eig(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, const EigWork& w,
                 int max_sweeps, double tol, hipStream_t st) {
   std::vector<JacobiJob> small, large;
@@ -928,8 +933,12 @@ int reduced_eig(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, const EigWork&
                         hipMemcpyHostToDevice, st));
   if (!small.empty()) {
     int maxm = 0;
-    for (const JacobiJob& j : small) maxm = std::max(maxm, j.m);
-    if (maxm >= kRoundJacobi) {
+    int64_t sum2 = 0;
+    for (const JacobiJob& j : small) {
+      maxm = std::max(maxm, j.m);
+      sum2 += (int64_t)j.m * j.m;
+    }
+    if (rounds_pay(maxm, sum2, device_cus())) {
       ProfScope ps(FB_PROF_JACOBI, st, 0.0);
       FB_TRY(round_jacobi(small, jobs_dev, max_sweeps, tol, st));
     } else {

@@ -62,11 +62,21 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
 
 // Hermitian eigensolver dispatch: matrices up to kSmallJacobi by the cyclic
 // Jacobi, larger ones by block Jacobi.  The cyclic Jacobi runs on one
-// workgroup per matrix, or, in a call with one of kRoundJacobi columns or
-// more, with a launch per round over the whole chip: the same bits, one
-// matrix of 64 columns 3.0 ms against 2.9, of 97 5.0 against 6.9.
+// workgroup per matrix or with a launch per round over the whole chip
+// (rounds_pay says which), with the same bits.
 constexpr int kSmallJacobi = 256;
 constexpr int kRoundJacobi = 80;
+// Whether a call whose largest matrix has maxm columns, with sum2 = sum of m^2
+// over its matrices, takes a launch per round.  One workgroup per matrix needs a
+// time of about maxm^3 whatever the number of matrices (up to the CUs); a
+// round needs its launch and a share for every element of every matrix.  ms, by
+// rounds against one workgroup each: 80 columns, 1 matrix 3.0 / 3.3, 8 3.2 /
+// 3.3, 16 3.4 / 3.3, 128 8.5 / 4.3; 96 columns, 32 5.9 / 6.1, 64 7.5 / 6.1;
+// 128 columns, 32 9.5 / 14, 64 16.4 / 15.8; 200 columns, 64 61 / 66, 128 122 /
+// 92; one of 250 with 128 of 79 22 / 108.  The line fits the crossings (9
+// matrices of 80 columns, 31 of 96, 52 of 128, 68 of 200); below kRoundJacobi
+// columns the two are within 5 %.
+bool rounds_pay(int maxm, int64_t sum2, int cus);
 struct EigWork {
   char* bj = nullptr;       // block Jacobi buffers
   void* dv = nullptr;       // descriptors

@@ -320,7 +320,7 @@ int eig_residuals(const Band& bd, const c128* X, int64_t ldx, const double* lam,
 // ||offdiag(A)||_F <= tol ||A||_F.  On exit w holds the eigenvalues in
 // ascending order and W the matching eigenvectors (columns of V sorted).
 static const int kJacThreads = 1024;
-static const int kJacMaxPairs = 2048;
+static const int kJacMaxPairs = kSmallJacobi / 2;  // reduced_eig sends no larger matrix
 
 __device__ __forceinline__ int rr_player(int pos, int r, int mp) {
   // circle method: position 0 fixed, the others rotate by r

@@ -847,12 +847,12 @@ int block_jacobi(const std::vector<JacobiJob>& jobs, const JacobiJob* jobs_dev, 
   // few pairs leave most of the chip idle: their U is then shared out over 2
   // or 4 workgroups each, as long as every workgroup has a CU of its own (a
   // second round of workgroups would cost more than the 18 % that it saves)
-  constexpr int kCUs = 256;
-  const int rlog = 4 * max_h * nj <= kCUs ? 4 : 2 * max_h * nj <= kCUs ? 5 : 6;
+  const int cus = rule_cus();
+  const int rlog = 4 * max_h * nj <= cus ? 4 : 2 * max_h * nj <= cus ? 5 : 6;
   const int upd_wgs = max_h * (max_h + 1) / 2 + max_h * (max_mp / kPb);
   // and tiles are split until there are four workgroups per CU
   const int64_t tiles = (int64_t)upd_wgs * nj;
-  const int csplit = 4 * tiles <= 4 * kCUs ? 4 : 2 * tiles <= 4 * kCUs ? 2 : 1;
+  const int csplit = 4 * tiles <= 4 * cus ? 4 : 2 * tiles <= 4 * cus ? 2 : 1;
   for (int sw = 0; sw <= max_sweeps; ++sw) {
     k_bj_norms<<<dim3(max_mp, nj), 256, 0, st>>>(dvd, cur);
     FB_HIP(hipGetLastError());
@@ -919,7 +919,7 @@ void carve_eig_work(Arena& ar, const std::vector<int>& ms, EigWork& w) {
 
 bool rounds_pay(int maxm, int64_t sum2, int cus) {
   const int64_t room = 80 * (int64_t)maxm * maxm - 450000;  // of 256 CUs
-  return maxm >= kRoundJacobi && 256 * sum2 <= room * (cus > 0 ? cus : 256);
+  return maxm >= kRoundJacobi && 256 * sum2 <= room * cus;
 }
 
 int reduced_eig(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, const EigWork& w,
@@ -938,7 +938,7 @@ int reduced_eig(std::vector<JacobiJob> jobs, JacobiJob* jobs_dev, const EigWork&
       maxm = std::max(maxm, j.m);
       sum2 += (int64_t)j.m * j.m;
     }
-    if (rounds_pay(maxm, sum2, device_cus())) {
+    if (rounds_pay(maxm, sum2, rule_cus())) {
       ProfScope ps(FB_PROF_JACOBI, st, 0.0);
       FB_TRY(round_jacobi(small, jobs_dev, max_sweeps, tol, st));
     } else {

@@ -186,6 +186,13 @@ int inertia_call(const fb_band* B, int32_t nshift, const double* shifts, int32_t
                  int32_t* n_zero, int32_t* n_pos, void* work, size_t* lwork, bool split,
                  void* stream);
 
+// compute units of the current device (a partition has fewer than the card), 0
+// where there is none
 int device_cus();
+// the number that dispatch rules count with
+inline int rule_cus() {
+  const int cus = device_cus();
+  return cus > 0 ? cus : 256;
+}
 
 }  // namespace fb

@@ -169,7 +169,7 @@ __device__ __forceinline__ void band_row(const c128* __restrict__ Bd, int64_t n,
   }
 }
 // columns per thread: four where that leaves a workgroup per CU
-static int band_cols(int64_t workgroups) { return workgroups >= 1024 ? 4 : 1; }
+static int band_cols(int64_t workgroups) { return workgroups >= 4 * rule_cus() ? 4 : 1; }
 
 template <int NC>
 __global__ void __launch_bounds__(kBmRows)

@@ -46,8 +46,7 @@ int solve_tile(int b, size_t tiles32) {
   const int nb = block_size(b);
   const int v = tuned_variant(sizeof(R), nb);
   if (v >= 0) return variant_tile(v);
-  constexpr size_t kCUs = 256;
-  return sizeof(R) == 4 && tiles32 >= kCUs && variant_fits(sizeof(R), nb, 2) ? 32 : 16;
+  return sizeof(R) == 4 && tiles32 >= (size_t)rule_cus() && variant_fits(sizeof(R), nb, 2) ? 32 : 16;
 }
 
 template <typename R>

@@ -17,7 +17,7 @@ inline size_t solve_lds_bytes(int nb, int t, size_t elem) {
   return (size_t)3 * nb * t * elem + (size_t)3 * nb * 2;
 }
 bool variant_fits(size_t rsize, int nb, int v);
-// the chosen variant, or -1
+// the chosen variant, or -1 (the rule chooses); setting -1 takes a choice back
 int tuned_variant(size_t rsize, int nb);
 void set_tuned_variant(size_t rsize, int nb, int v);
 

@@ -567,11 +567,11 @@ __global__ void k_bj_rank(const JacobiJob* __restrict__ jobs, BJDev* __restrict_
   const c128* A = (cur ? d.A[1] : d.A[0]);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= d.mp) return;
-  const double wi = gld(A + (int64_t)i * d.mp + i).x;
+  const double wi = gld(A + (int64_t)i * d.mp + i).x, ki = rank_key(wi);
   int rank = 0;
   for (int j = 0; j < d.mp; ++j) {
-    const double wj = gld(A + (int64_t)j * d.mp + j).x;
-    rank += (wj < wi || (wj == wi && j < i)) ? 1 : 0;
+    const double wj = rank_key(gld(A + (int64_t)j * d.mp + j).x);
+    rank += (wj < ki || (wj == ki && j < i)) ? 1 : 0;
   }
   if (rank < d.m) {
     gst(jb.w + rank, wi);
@@ -747,9 +747,12 @@ __global__ void __launch_bounds__(1024) k_jr_final(const JacobiJob* __restrict__
   for (int i = t; i < m; i += 1024) d[i] = gld(&A[(int64_t)i * lda + i].x);
   __syncthreads();
   for (int i = t; i < m; i += 1024) {
-    const double wi = d[i];
+    const double wi = d[i], ki = rank_key(wi);
     int rank = 0;
-    for (int j = 0; j < m; ++j) rank += (d[j] < wi || (d[j] == wi && j < i)) ? 1 : 0;
+    for (int j = 0; j < m; ++j) {
+      const double kj = rank_key(d[j]);
+      rank += (kj < ki || (kj == ki && j < i)) ? 1 : 0;
+    }
     gst(jb.w + rank, wi);
     gst(jb.order + rank, i);
   }

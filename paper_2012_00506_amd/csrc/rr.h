@@ -22,6 +22,10 @@ struct JacobiJob {
   int32_t* sweeps;// out (may be null)
 };
 
+// Eigenvalues are ranked ascending, ties by column; a NaN ranks as an infinity, so
+// that the ranks are a permutation whatever the values.
+__device__ __forceinline__ double rank_key(double w) { return fmin(w, __builtin_inf()); }
+
 int fill_zero(c128* p, int64_t rows, int64_t cols, int64_t ld, hipStream_t st);
 
 // Q += sum_p w_p X_p over the (node, direction) solutions of one slice, in

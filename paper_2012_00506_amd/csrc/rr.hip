@@ -444,11 +444,11 @@ k_jacobi(JacobiJob* __restrict__ jobs, int max_sweeps, double tol) {
   }
   // eigenvalues ascending (rank by value, ties by index), vectors follow
   for (int i = t; i < m; i += blockDim.x) {
-    double wi = A[(int64_t)i * lda + i].x;
+    double wi = A[(int64_t)i * lda + i].x, ki = rank_key(wi);
     int rank = 0;
     for (int j = 0; j < m; ++j) {
-      double wj = A[(int64_t)j * lda + j].x;
-      rank += (wj < wi || (wj == wi && j < i)) ? 1 : 0;
+      double wj = rank_key(A[(int64_t)j * lda + j].x);
+      rank += (wj < ki || (wj == ki && j < i)) ? 1 : 0;
     }
     jb.w[rank] = wi;
     jb.order[rank] = i;

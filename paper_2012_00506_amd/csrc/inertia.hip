@@ -21,9 +21,9 @@
 // columns per panel are one MFMA depth: wider panels need a longer serial
 // factorisation of their diagonal block, narrower ones waste the instruction.
 // Measured, one unblocked rank-one update per barrier before -> this kernel
-// with the split below: complex n = 16384, b = 64, 17 shifts 29.3 -> 3.2 ms;
-// real n = 12288, b = 113, 64 shifts 54.9 -> 1.8 ms; real n = 512, b = 8,
-// 2 shifts 0.40 -> 0.09 ms.
+// with the split below: complex n = 16384, b = 64, 17 shifts 29.3 -> 3.5 ms;
+// real n = 12288, b = 113, 64 shifts 54.9 -> 2.0 ms; real n = 512, b = 8,
+// 2 shifts 0.40 -> 0.095 ms.
 //
 // With few shifts the chain is also cut in two: one workgroup eliminates the
 // leading rows downwards, another the trailing rows upwards (the same code on

@@ -32,8 +32,8 @@
 // In exact arithmetic every elimination order gives the same inertia as long
 // as no pivot is zero, but without pivoting the digits that an order keeps
 // depend on its smallest pivots.  A shift that meets a zero pivot, or one below
-// sqrt(eps) ||B||_1 on the way up or in the separator, is redone in the plain
-// order, leading rows first, whose counts are the documented ones.
+// 2^-34 ||B||_1 on the way up or in the separator, is redone in the plain order,
+// leading rows first, whose counts are the documented ones.
 #include <type_traits>
 
 #include "fb_internal.h"
@@ -49,6 +49,14 @@ constexpr int kInertiaThreads = 64 * kWaves;
 constexpr size_t kLdsBudget = 160 * 1024;
 // shifts that a launch splits in two halves: their workgroups fill the chip
 constexpr int kSplitShifts = 128;
+// A pivot below kZero ||B||_1 is a zero one.  In the orders that only the split
+// has, one below kSmall ||B||_1, which lets the elements grow until two thirds of
+// their digits are lost, is reported as such, so that the plain order is taken.
+// (Ordinary matrices have such pivots too, one in 1e9 or so; with 2^-26, one in 6
+// million, every second launch of 128 shifts at n = 65536, b = 128 would meet
+// one and be redone.)
+constexpr double kZero = 0x1p-104;
+constexpr double kSmall = 0x1p-34;
 
 // ---- element types: complex Hermitian or real symmetric
 __device__ __forceinline__ double re_of(double a) { return a; }
@@ -144,6 +152,7 @@ struct InertiaArgs {
   int32_t* counts;  // 3 per shift
   int mode;
   int gated;        // kFull: only shifts whose counts hold a zero or small pivot
+  double tiny[2];   // relative limit of a zero pivot, downwards and upwards
   int h0, h1;       // blocks of 16 rows eliminated from the top and the bottom
   int32_t* part;    // 4 per shift: (neg, zero) of the two halves
   c128* dump;       // 2 per shift: the window left by a half, tile by tile
@@ -197,11 +206,7 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
   const int b = a.b;
   const c128* Bd = a.Bd;
   const double sigma = a.shifts[s];
-  const double eps = 2.220446049250313e-16;
-  // the orders that only the split has: a pivot below sqrt(eps) ||B||_1 lets
-  // the elements grow until half their digits are lost, and is reported as a
-  // zero one, for which the plain order is taken
-  const double pivmin = (half || a.mode == kMiddle ? 0x1p-26 : eps * eps) * a.stats[0];
+  const double pivmin = a.tiny[half] * a.stats[0];
   // rows of this elimination and of them the ones it eliminates
   const int64_t sep0 = (int64_t)16 * a.h0;                       // first separator row
   const int64_t S = n - (int64_t)16 * (a.h0 + a.h1);             // separator rows
@@ -535,6 +540,7 @@ int launch_inertia(const Band& bd, int nshift, const double* shifts_dev, int32_t
   a.shifts = shifts_dev;
   a.stats = bd.stats;
   a.counts = cnt_dev;
+  a.tiny[0] = kZero;
   auto go = [&](int grid) {
     return bd.cplx ? launch_any<true>(a, tiles, grid, st) : launch_any<false>(a, tiles, grid, st);
   };
@@ -550,10 +556,13 @@ int launch_inertia(const Band& bd, int nshift, const double* shifts_dev, int32_t
   const int64_t blocks = (bd.n - bd.b) / 16;  // the separator keeps b .. b + 15 rows
   a.h0 = (int)((blocks + 1) / 2);
   a.h1 = (int)(blocks / 2);
+  a.tiny[1] = kSmall;
   a.mode = kHalves;
   FB_TRY(go(2 * nshift));
+  a.tiny[0] = kSmall;
   a.mode = kMiddle;
   FB_TRY(go(nshift));
+  a.tiny[0] = kZero;
   a.mode = kFull;
   a.gated = 1;
   return go(nshift);

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows", [1, 2, 8, 12])
-@pytest.mark.parametrize("noise", [1e-25, 3e-17, 1e-12])
+@pytest.mark.parametrize("noise", [1e-25, 3e-17, 1e-12, 1e-9])
 @pytest.mark.parametrize("cplx", [False, True])
 def test_trailing_rows_with_a_diagonal_block_of_noise(rows, noise, cplx):
     import paper_2012_00506_amd as fb

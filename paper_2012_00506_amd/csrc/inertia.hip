@@ -207,6 +207,7 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
   const c128* Bd = a.Bd;
   const double sigma = a.shifts[s];
   const double pivmin = a.tiny[half] * a.stats[0];
+  const double pad = 1.0 + 2.0 * pivmin;  // a pivot that is never tiny
   // rows of this elimination and of them the ones it eliminates
   const int64_t sep0 = (int64_t)16 * a.h0;                       // first separator row
   const int64_t S = n - (int64_t)16 * (a.h0 + a.h1);             // separator rows
@@ -221,15 +222,15 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
   }
 
   // A(i, i - d) of the shifted band in this elimination's row order (the
-  // reversed half reads the conjugate, which has the same inertia); identity
-  // beyond the last row.  Out-of-range elements read element 0 and are
+  // reversed half reads the conjugate, which has the same inertia); pad on the
+  // diagonal beyond the last row.  Out-of-range elements read element 0 and are
   // replaced, so that the loads stay branch-free.
   auto band_off = [&](int64_t i, int d) -> int64_t {
     const bool ok = d >= 0 && d <= b && i < n && i - d >= 0;
     return ok ? (int64_t)d * n + (half ? n - 1 - i : i - d) : 0;
   };
   auto band_val = [&](E v, int64_t i, int d) -> E {
-    if (i >= n) return Ld::real(d == 0 ? 1.0 : 0.0);
+    if (i >= n) return Ld::real(d == 0 ? pad : 0.0);
     if (d < 0 || d > b) return Ld::real(0.0);
     if (d == 0) return Ld::real(re_of(v) - sigma);
     return v;
@@ -257,7 +258,7 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
       E v;
       if (a.mode == kMiddle) {
         if (i >= S || j >= S) {
-          v = Ld::real(d == 0 ? 1.0 : 0.0);
+          v = Ld::real(d == 0 ? pad : 0.0);
         } else if (d < 0) {
           v = Ld::real(0.0);
         } else {
@@ -287,10 +288,9 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
   for (int e = t; e < kEnter<T>; e += kInertiaThreads) lput(El + e, Ld::real(0.0));
 
   int neg = 0, zero = 0, par = 0;
-  // whole blocks: the columns past the last are the identity's, whose pivots
-  // are positive, or tiny where pivmin is above 1
+  // whole blocks: the columns past the last are the padding's, whose pivots
+  // count as positive
   const int nblk = (int)((ncols + 15) / 16);
-  if (pivmin > 1.0) zero -= (int)(16 * (int64_t)nblk - ncols);
   constexpr int NPF = T;  // (16 (T - 1) + 1) 16 entries over 256 threads
   E pf[NPF];
   const c128* pfp[NPF];  // this thread's entries of the next block row to enter
@@ -307,20 +307,18 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
     // entering block row, fetched over the block's four panels
     const bool last = a.mode != kHalves && blk + 1 == nblk;
     const int64_t X16 = 16 * ((int64_t)blk + T);
-    int inside = 16;  // of its rows
     if (!last) {
       if (X16 + 16 <= n) {
 #pragma unroll
         for (int q = 0; q < NPF; ++q) pf[q] = Ld::load(pfp[q]);
       } else {
-        // rows past the last: the identity's
-        inside = X16 < n ? (int)n & 15 : 0;
+        // rows past the last: a diagonal of at least pad once sigma is off it
 #pragma unroll
         for (int q = 0; q < NPF; ++q) {
           const int e = t + q * kInertiaThreads;
           const bool in = X16 + (e & 15) < n;
           pf[q] = Ld::load(in ? pfp[q] : Bd);
-          if (!in) pf[q] = Ld::real(e < 16 ? 1.0 : 0.0);
+          if (!in) pf[q] = Ld::real(e < 16 ? pad + 2.0 * fabs(sigma) : 0.0);
         }
       }
 #pragma unroll
@@ -395,7 +393,7 @@ __global__ void __launch_bounds__(kInertiaThreads, 1) k_band_inertia(InertiaArgs
             asm volatile("" : "+v"(x.x), "+v"(x.y));
           else
             asm volatile("" : "+v"(x));
-          if (q == 0 && t < inside) x = Ld::real(re_of(x) - sigma);
+          if (q == 0 && t < 16) x = Ld::real(re_of(x) - sigma);
           lput(Wl + pfl[q], x);
         }
       }

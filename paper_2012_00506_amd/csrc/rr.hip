@@ -142,8 +142,8 @@ static const int kBmRows = 256;
 // x + q ld (q < nc; the rest repeat column nc - 1): the sum runs over the
 // diagonals, below before above.  inner: every neighbour is a row of B.
 // What bounds it: B's diagonals, 16 bytes from L2 per multiply-add of a column;
-// with four columns per thread they are read once for all four.  n = 16384, b =
-// 64, 600 columns: residuals 1.66 -> 1.20 ms, products 1.33 -> 1.12.
+// with four columns per thread they are read once for all four, by a quarter of
+// the threads.
 template <int NC>
 __device__ __forceinline__ void band_row(const c128* __restrict__ Bd, int64_t n, int b,
                                          const c128* const (&x)[NC], int64_t i, bool inner,
@@ -168,8 +168,10 @@ __device__ __forceinline__ void band_row(const c128* __restrict__ Bd, int64_t n,
     }
   }
 }
-// columns per thread: four where that leaves a workgroup per CU
-static int band_cols(int64_t workgroups) { return workgroups >= 4 * rule_cus() ? 4 : 1; }
+// columns per thread: four where that leaves wgs workgroups
+static int band_cols(int64_t chunks, int m, int64_t wgs) {
+  return chunks * ((m + 3) / 4) >= wgs ? 4 : 1;
+}
 
 template <int NC>
 __global__ void __launch_bounds__(kBmRows)
@@ -201,7 +203,11 @@ int band_matmul(const Band& bd, const c128* X, int64_t ldx, c128* Y, int64_t ldy
   for (int c0 = 0; c0 < m; c0 += 65535) {
     int mc = std::min(65535, m - c0);
     const unsigned rows = (unsigned)((bd.n + kBmRows - 1) / kBmRows);
-    if (band_cols((int64_t)rows * mc) == 4)
+    // 16 workgroups per CU.  us with one and four columns per thread: n = 16384,
+    // b = 64, 70 columns (1152 workgroups of four) 150, 160; 260 (4160) 523, 515;
+    // 600 (9600) 1228, 1150; n = 4000, b = 8, 260 (1040) 23, 24; n = 300000, b =
+    // 64, 1 (1172) 87, 165
+    if (band_cols(rows, mc, 16 * (int64_t)rule_cus()) == 4)
       k_band_matmul<4><<<dim3(rows, (mc + 3) / 4), kBmRows, 0, st>>>(
           bd.Bd, bd.n, bd.b, X + (int64_t)c0 * ldx, ldx, Y + (int64_t)c0 * ldy, ldy, mc);
     else
@@ -293,7 +299,10 @@ int eig_residuals(const Band& bd, const c128* X, int64_t ldx, const double* lam,
   int nchunk = (int)((bd.n + kErChunk - 1) / kErChunk);
   for (int c0 = 0; c0 < m; c0 += 65535) {
     int mc = std::min(65535, m - c0);
-    if (band_cols((int64_t)nchunk * mc) == 4)
+    // three workgroups per two CUs (each takes 16 rows per thread).  us as above:
+    // n = 16384, b = 64, 260 columns (260 workgroups of four) 634, 777; 400 (400)
+    // 930, 858; 600 (600) 1321, 1127; n = 300000, b = 64, 4 (74) 317, 992
+    if (band_cols(nchunk, mc, 3 * (int64_t)rule_cus() / 2) == 4)
       k_eig_resid_part<4><<<dim3(nchunk, (mc + 3) / 4), 256, 0, st>>>(
           bd.Bd, bd.n, bd.b, X + (int64_t)c0 * ldx, ldx, lam + c0,
           part + (size_t)c0 * nchunk * 2, mc, nchunk);
